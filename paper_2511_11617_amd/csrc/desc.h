@@ -30,6 +30,8 @@ enum : uint32_t {
   DF_ALIGNED = 1u << 7,   // every offset, pitch, stride and run is a
                           // multiple of 16: the 16-byte vector kernel
   DF_WIDE = 1u << 8,      // aligned, tiled kWideUnroll chunks per thread
+  DF_SRC_GRID = 1u << 9,  // not aligned: chunks start at 16-byte boundaries
+                          // of the source, not of the destination
 };
 
 // Launch shape of the vector kernel: 256 threads, ATP_UNROLL independent
@@ -62,8 +64,14 @@ constexpr int64_t kWideTileChunks = kThreads * kWideUnroll;
 constexpr uint64_t kWideMaxRun = 4096;
 // 16-byte chunks per tile of a vector-kernel descriptor
 constexpr int64_t tile_chunks(uint32_t flags) { return (flags & DF_WIDE) ? kWideTileChunks : kTileChunks; }
-// bytes per tile of the 2-byte-granular (LDS funnel-shift) kernel
-constexpr int64_t kSegBytes = 8192;
+// Chunks per line of a descriptor.  A line that is not aligned is cut at the
+// 16-byte boundaries of one side (DF_SRC_GRID), its first and last chunk
+// overlapping their neighbours: at most ceil((run + 15) / 16) chunks,
+// wherever the line starts.  A run shorter than one chunk is one chunk,
+// copied byte by byte.
+constexpr uint32_t line_chunks(uint64_t run, uint32_t flags) {
+  return uint32_t((flags & DF_ALIGNED) ? run >> 4 : run < 16 ? 1 : (run + 30) >> 4);
+}
 
 struct alignas(16) Desc {
   uint64_t src_off, dst_off;
@@ -71,11 +79,11 @@ struct alignas(16) Desc {
   uint64_t src_ostride, dst_ostride;
   int64_t o_begin, o_end;
   uint32_t run, rows;
-  uint32_t flags, pad;
-  // exact 32-bit division by a host-known divisor d >= 2:
-  // q = umulhi64(n, m) with m = ceil(2^64 / d); m = 0 means d == 1
-  uint64_t magic_line;  // divisor: 16-byte chunks per line (vector kernel)
-                        //          or segments per line (2-byte kernel)
+  uint32_t flags;
+  uint32_t cpl;         // chunks per line (line_chunks)
+  // exact division by a host-known divisor d >= 2: q = umulhi64(n, m) with
+  // m = ceil(2^64 / d), for n * d < 2^64; m = 0 means d == 1
+  uint64_t magic_line;  // divisor: cpl
   uint64_t magic_rows;  // divisor: rows
 };
 

@@ -348,10 +348,8 @@ void build_descs(Exec &E, const CallPlan &c, CallState &cs) {
     d.run = uint32_t(f.run);
     d.rows = uint32_t(f.rows);
     d.flags = f.flags;
-    if (f.flags & DF_ALIGNED)
-      d.magic_line = magic_of(f.run / 16);
-    else
-      d.magic_line = magic_of((f.run + kSegBytes - 1) / kSegBytes);
+    d.cpl = line_chunks(f.run, f.flags);
+    d.magic_line = magic_of(d.cpl);
     d.magic_rows = magic_of(f.rows);
     cs.desc_host[i] = d;
   }
@@ -435,7 +433,7 @@ void launch_copy(Exec &E, const Launch &L, const Desc *dev_desc, const int64_t *
     hipLaunchKernelGGL((k_copy16<kUnroll>), dim3(unsigned(g)), dim3(kThreads), 0, s, dev_desc, dev_prefix, L.d0,
                        L.d1, b0, b1, b2, live);
   else
-    hipLaunchKernelGGL(k_copy_bytes, dim3(unsigned(g)), dim3(kThreads), 0, s, dev_desc, dev_prefix, L.d0, L.d1, b0,
+    hipLaunchKernelGGL(k_copy_any, dim3(unsigned(g)), dim3(kThreads), 0, s, dev_desc, dev_prefix, L.d0, L.d1, b0,
                        b1, b2, live);
   HIPCHK(hipGetLastError());
 }
@@ -1098,7 +1096,7 @@ void exec_warmup(void *compute_, void *copy_, int events) {
   hipFuncAttributes fa;
   HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy16<kUnroll>)));
   HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy16<kWideUnroll>)));
-  HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy_bytes)));
+  HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy_any)));
   HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_prepare)));
   HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_spin)));
   HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_nop)));

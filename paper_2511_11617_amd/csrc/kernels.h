@@ -10,11 +10,9 @@
 //   k_copy16      descriptor-driven copy in 16-byte chunks, 2 independent
 //                 loads in flight per thread, non-temporal hints; a tile is
 //                 512 consecutive chunks (8 KiB) of one descriptor.
-//   k_copy_bytes  the same for runs that are not 16-byte aligned (odd
-//                 column counts): a tile stages one 8 KiB line segment in
-//                 LDS with aligned 16-byte loads and writes it out with
-//                 aligned 16-byte stores, funnel-shifting bytes between
-//                 neighbouring LDS words; ragged ends use byte stores.
+//   k_copy_any    the same for lines that are not 16-byte aligned (odd column
+//                 counts): unaligned 16-byte accesses on one side, the
+//                 chunks of a line cut at the other side's boundaries.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -29,6 +27,11 @@ enum : int32_t { ERR_BAD_BLOCK = 1, ERR_LIVE_COUNT = 2 };
 
 __device__ __forceinline__ uint32_t divq(uint32_t n, uint64_t magic) {
   return magic ? uint32_t(__umul64hi(uint64_t(n), magic)) : n;
+}
+
+// The same for a dividend past 32 bits whose quotient fits them.
+__device__ __forceinline__ uint32_t divl(uint64_t n, uint64_t magic) {
+  return uint32_t(magic ? __umul64hi(n, magic) : n);
 }
 
 __device__ __forceinline__ char *slot_base(uint32_t slot, char *b0, char *b1, char *b2) {
@@ -132,11 +135,7 @@ __global__ void __launch_bounds__(1024) k_prepare(PrepArgs a) {
     }
     if (bad) x.o_end = x.o_begin;  // an invalid table moves nothing
     uint64_t lines = uint64_t(x.o_end - x.o_begin) * x.rows;
-    uint64_t tiles;
-    if (x.flags & DF_ALIGNED)
-      tiles = (lines * (x.run >> 4) + tile_chunks(x.flags) - 1) / tile_chunks(x.flags);
-    else
-      tiles = lines * ((x.run + kSegBytes - 1) / kSegBytes);
+    const uint64_t tiles = (lines * x.cpl + tile_chunks(x.flags) - 1) / tile_chunks(x.flags);
     a.prefix[d] = int64_t(tiles);  // temporarily the count
     sum += int64_t(tiles);
   }
@@ -246,7 +245,7 @@ __global__ void __launch_bounds__(kThreads) k_copy16(const Desc *__restrict__ de
   for (int64_t t = T0 + tile_of_block(); t < T1; t += gridDim.x) {
     const int d = find_desc(prefix, d0, d1, t);
     const Desc x = descs[d];
-    const uint32_t cpl = x.run >> 4;
+    const uint32_t cpl = x.cpl;
     const uint64_t total = uint64_t(x.o_end - x.o_begin) * x.rows * cpl;
     const uint64_t cbase = uint64_t(t - prefix[d]) * kTile;
     const uint64_t clast = (cbase + kTile < total ? cbase + kTile : total) - 1;
@@ -305,66 +304,82 @@ __global__ void __launch_bounds__(kThreads) k_copy16(const Desc *__restrict__ de
   }
 }
 
-__global__ void __launch_bounds__(kThreads) k_copy_bytes(const Desc *__restrict__ descs,
-                                                         const int64_t *__restrict__ prefix, int d0, int d1, char *b0,
-                                                         char *b1, char *b2, const int32_t *__restrict__ live) {
-  __shared__ uint32_t lds[kSegBytes / 4 + 16];
+// Lines that are not 16-byte aligned.  Unaligned 16-byte accesses are
+// ordinary global memory operations here, so the bytes need no staging in
+// LDS: a chunk starts at a 16-byte boundary of one side, which makes that
+// side's accesses aligned, the other side is accessed wherever it falls, and
+// the first and last chunk of a line are moved inwards so that all of their
+// 16 bytes lie in the line (they repeat bytes of their neighbours, the same
+// values).  The aligned side is the pinned host buffer of a host read
+// (DF_SRC_GRID: a request that crosses a 64-byte line costs two PCIe reads)
+// and the destination otherwise.  Tiles are consecutive chunks of one
+// descriptor, as in k_copy16, so short lines share a workgroup: bound by the
+// link or by HBM like the aligned ones.  Measured against one workgroup per
+// line through LDS: host reads of 5 KB / 700 B / 344 B lines 19 / 2.8 / 1.5
+// -> 57 / 56 / 54 GB/s; HBM copies of the same lines (read + write) 3.7 /
+// 0.65 / 0.34 -> 4.8 / 3.2 / 2.7 TB/s at 306 / 124 / 71 MB.  Tiles of twice
+// the width, and source boundaries for the HBM copies, were 0-9 % slower.
+typedef u32x4 __attribute__((address_space(1), aligned(1))) global_u32x4_any;
+typedef unsigned char __attribute__((address_space(1))) global_u8;
+
+__device__ __forceinline__ u32x4 load16_any(const char *p) {
+  return __builtin_nontemporal_load((const global_u32x4_any *)(p));
+}
+__device__ __forceinline__ void store16_any(char *p, u32x4 v) {
+  __builtin_nontemporal_store(v, (global_u32x4_any *)(p));
+}
+
+__global__ void __launch_bounds__(kThreads) k_copy_any(const Desc *__restrict__ descs,
+                                                       const int64_t *__restrict__ prefix, int d0, int d1, char *b0,
+                                                       char *b1, char *b2, const int32_t *__restrict__ live) {
+  constexpr int U = kUnroll;
   const int64_t T0 = prefix[d0], T1 = prefix[d1];
-  const int tid = threadIdx.x;
-  for (int64_t t = T0 + blockIdx.x; t < T1; t += gridDim.x) {
+  const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (int64_t t = T0 + tile_of_block(); t < T1; t += gridDim.x) {
     const int d = find_desc(prefix, d0, d1, t);
     const Desc x = descs[d];
-    const uint32_t spl = uint32_t((x.run + kSegBytes - 1) / kSegBytes);
-    const uint32_t tin = uint32_t(t - prefix[d]);
-    const uint32_t line = divq(tin, x.magic_line);
-    const uint32_t seg = tin - line * spl;
-    LineAddr la = line_addr<true>(x, line, b0, b1, b2, live);
-    const uint64_t skip = uint64_t(seg) * kSegBytes;
-    const char *src = la.src + skip;
-    char *dst = la.dst + skip;
-    const uint32_t n = uint32_t((x.run - skip) < uint64_t(kSegBytes) ? (x.run - skip) : kSegBytes);
-    // stage [src, src + n) through LDS in aligned 16-byte groups
-    const uintptr_t s_al = uintptr_t(src) & ~uintptr_t(15);
-    const uint32_t head = uint32_t(uintptr_t(src) - s_al);
-    const uint32_t ngroups = (head + n + 15) >> 4;
-    for (uint32_t g = tid; g < ngroups; g += kThreads) {
-      u32x4 w = *reinterpret_cast<const u32x4 *>(s_al + 16 * uintptr_t(g));
-      lds[4 * g + 0] = w.x;
-      lds[4 * g + 1] = w.y;
-      lds[4 * g + 2] = w.z;
-      lds[4 * g + 3] = w.w;
-    }
-    __syncthreads();
-    const uintptr_t d_lo = uintptr_t(dst), d_hi = d_lo + n;
-    uintptr_t a_lo = (d_lo + 15) & ~uintptr_t(15), a_hi = d_hi & ~uintptr_t(15);
-    if (a_lo > a_hi) a_lo = a_hi = d_hi;  // no whole aligned chunk inside
-    const uint32_t nfull = uint32_t((a_hi - a_lo) >> 4);
-    for (uint32_t ch = tid; ch < nfull; ch += kThreads) {
-      const uint32_t off = head + uint32_t(a_lo - d_lo) + 16 * ch;  // byte offset in the staged window
-      const uint32_t w0 = off >> 2, sh = off & 3;
-      u32x4 o;
-      if (sh == 0) {
-        o.x = lds[w0];
-        o.y = lds[w0 + 1];
-        o.z = lds[w0 + 2];
-        o.w = lds[w0 + 3];
-      } else {
-        const uint32_t l0 = lds[w0], l1 = lds[w0 + 1], l2 = lds[w0 + 2], l3 = lds[w0 + 3], l4 = lds[w0 + 4];
-        o.x = __builtin_amdgcn_alignbyte(l1, l0, sh);
-        o.y = __builtin_amdgcn_alignbyte(l2, l1, sh);
-        o.z = __builtin_amdgcn_alignbyte(l3, l2, sh);
-        o.w = __builtin_amdgcn_alignbyte(l4, l3, sh);
+    const uint64_t total = uint64_t(x.o_end - x.o_begin) * x.rows * x.cpl;
+    const uint64_t cbase = uint64_t(t - prefix[d]) * kTileChunks;
+    const uint64_t clast = (cbase + kTileChunks < total ? cbase + kTileChunks : total) - 1;
+    if (x.run < 16) {
+      for (uint64_t c = cbase + threadIdx.x; c <= clast; c += kThreads) {
+        const LineAddr la = line_addr<false>(x, uint32_t(c), b0, b1, b2, live);
+        for (uint32_t i = 0; i < x.run; ++i) ((global_u8 *)la.dst)[i] = ((const global_u8 *)la.src)[i];
       }
-      __builtin_nontemporal_store(o, reinterpret_cast<u32x4 *>(a_lo) + ch);
+      continue;
     }
-    // ragged ends, one byte per thread
-    const uint32_t nhead = uint32_t(a_lo - d_lo), ntail = uint32_t(d_hi - a_hi);
-    const unsigned char *lb = reinterpret_cast<const unsigned char *>(lds);
-    for (uint32_t i = tid; i < nhead + ntail; i += kThreads) {
-      const uint32_t pos = i < nhead ? i : uint32_t(a_hi - d_lo) + (i - nhead);
-      reinterpret_cast<unsigned char *>(d_lo)[pos] = lb[head + pos];
+    const char *sp[U];
+    char *dp[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const uint64_t g0r = cbase + uint64_t(k) * kThreads + wv * 64;
+      const uint64_t g0 = g0r < clast ? g0r : clast;
+      const uint64_t gl = g0r + 63 < clast ? g0r + 63 : clast;
+      const uint64_t cr = cbase + threadIdx.x + uint64_t(k) * kThreads;
+      const uint64_t c = cr < clast ? cr : clast;
+      const uint32_t lf = divl(g0, x.magic_line);
+      LineAddr la;
+      uint32_t col;
+      if (lf == divl(gl, x.magic_line)) {
+        la = line_addr<true>(x, lf, b0, b1, b2, live);
+        col = uint32_t(c - uint64_t(lf) * x.cpl);
+      } else {
+        const uint32_t line = divl(c, x.magic_line);
+        la = line_addr<false>(x, line, b0, b1, b2, live);
+        col = uint32_t(c - uint64_t(line) * x.cpl);
+      }
+      const uint32_t h = uint32_t(uintptr_t((x.flags & DF_SRC_GRID) ? la.src : la.dst)) & 15;
+      const int32_t o = int32_t(col * 16) - int32_t(h), omax = int32_t(x.run) - 16;
+      const int32_t off = o < 0 ? 0 : (o > omax ? omax : o);
+      sp[k] = la.src + off;
+      dp[k] = la.dst + off;
     }
-    __syncthreads();
+    u32x4 v[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) v[k] = load16_any(sp[k]);
+#pragma unroll
+    for (int k = 0; k < U; ++k)
+      if (cbase + threadIdx.x + uint64_t(k) * kThreads <= clast) store16_any(dp[k], v[k]);
   }
 }
 

@@ -743,23 +743,22 @@ bool fam_aligned(const Fam &f) {
 
 // Tiles of a family whose DF_ALIGNED / DF_WIDE flags are set.
 uint64_t fam_tiles(const Fam &f, int64_t items_hint) {
-  uint64_t lines = uint64_t(items_hint) * f.rows;
-  if (f.flags & DF_ALIGNED) {
-    uint64_t chunks = lines * (f.run / 16);
-    return (chunks + uint64_t(tile_chunks(f.flags)) - 1) / uint64_t(tile_chunks(f.flags));
-  }
-  return lines * ((f.run + kSegBytes - 1) / kSegBytes);
+  const uint64_t chunks = uint64_t(items_hint) * f.rows * line_chunks(f.run, f.flags);
+  return (chunks + uint64_t(tile_chunks(f.flags)) - 1) / uint64_t(tile_chunks(f.flags));
 }
 
 // Emit launches for a group of families: aligned ones first (with wide
-// tiles, if `allow_wide`, for short KV lines), then the 2-byte-granular ones.
+// tiles, if `allow_wide`, for short KV lines), then the ones that are not.
 // Families are appended to c.fams; every family of a launch has the same
 // DF_ALIGNED and DF_WIDE flags.
 void emit_group(CallPlan &c, std::vector<Fam> group, int level, int kind, std::vector<Launch> &out,
                 int64_t live_hint, bool allow_wide) {
   for (Fam &f : group) {
-    f.flags &= ~(DF_ALIGNED | DF_WIDE);
-    if (!fam_aligned(f)) continue;
+    f.flags &= ~(DF_ALIGNED | DF_WIDE | DF_SRC_GRID);
+    if (!fam_aligned(f)) {
+      if (kind == 4) f.flags |= DF_SRC_GRID;  // reads of the pinned host buffer
+      continue;
+    }
     f.flags |= DF_ALIGNED;
     if (allow_wide && f.run <= kWideMaxRun && (f.flags & (DF_SRC_IND | DF_DST_IND | DF_BLOCKRANGE)))
       f.flags |= DF_WIDE;

@@ -85,7 +85,7 @@ struct HostCopy {
 struct Chunk {
   int slot = 0;
   std::vector<HostCopy> copies;   // into the slot
-  std::vector<Launch> scatters;   // aligned and/or 2-byte-granular
+  std::vector<Launch> scatters;   // aligned, wide and unaligned ones
 };
 
 // Everything one reshard call (weights or KV) executes.
