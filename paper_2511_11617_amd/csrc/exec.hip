@@ -769,14 +769,14 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
   if (kvcall) {
     pa.table = table;
     pa.n_entries = n_entries;
-    pa.flags = reinterpret_cast<int32_t *>(b_st + c.off_kvflags);
-    pa.pref = reinterpret_cast<int32_t *>(b_st + c.off_kvpref);
+    pa.mask = reinterpret_cast<uint64_t *>(b_st + c.off_kvmask);
+    pa.rank = reinterpret_cast<int32_t *>(b_st + c.off_kvrank);
     pa.live = dev_live;
     pa.n_blocks = P.kv.num_blocks;
     pa.expect_live = P.kv.live_blocks;
   }
   // k_prepare is the only writer of the error word: it stores it once
-  hipLaunchKernelGGL(k_prepare, dim3(1), dim3(1024), 0, compute, pa);
+  hipLaunchKernelGGL(k_prepare, dim3(1), dim3(kPrepThreads), 0, compute, pa);
   HIPCHK(hipGetLastError());
   is.other(compute);
   hipEvent_t prepared = nullptr;  // descriptors, prefix sums and live blocks in place

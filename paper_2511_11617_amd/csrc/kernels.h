@@ -75,50 +75,127 @@ struct PrepArgs {
   int32_t *err;          // error word (meta area)
   const int32_t *table;  // block table, n_entries int32
   int64_t n_entries;
-  int32_t *flags;        // [n_blocks]
-  int32_t *pref;         // [n_blocks + 1]
+  uint64_t *mask;        // [ceil(n_blocks / 64)] live blocks of each group of 64 ids
+  int32_t *rank;         // [ceil(n_blocks / 64)] live blocks before each group
   int32_t *live;         // [n_blocks] sorted live block ids
   int64_t n_blocks;
   int64_t expect_live;
 };
 
-__global__ void __launch_bounds__(1024) k_prepare(PrepArgs a) {
+// Live ids below b: the position in the live list where block b's would be.
+__device__ __forceinline__ int64_t live_rank(const PrepArgs &a, int64_t b, int64_t total) {
+  if (b <= 0) return 0;
+  if (b >= a.n_blocks) return total;
+  return a.rank[b >> 6] + __popcll(a.mask[b >> 6] & ((uint64_t(1) << (b & 63)) - 1));
+}
+
+// Block ids one pass of k_prepare marks: a byte each in LDS.
+constexpr int kPrepWindow = 1 << 16;
+constexpr int kPrepThreads = 1024;
+constexpr int kPrepGroups = 8;  // groups of 64 ids in flight per wave
+
+// Table entries [e, e + 1024 K), K loads in flight per thread: marks the ids
+// in [w0, w0 + n) and keeps the largest id seen.
+template <int K>
+__device__ __forceinline__ void mark_blocks(const PrepArgs &a, int64_t e, int64_t w0, int n, uint8_t *flag,
+                                            int32_t *top) {
+  int32_t v[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int64_t i = e + threadIdx.x + int64_t(k) * kPrepThreads;
+    v[k] = a.table[i < a.n_entries ? i : a.n_entries - 1];
+  }
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    *top = v[k] > *top ? v[k] : *top;
+    const uint32_t p = uint32_t(v[k]) - uint32_t(w0);  // an id of -1 or below lands past n
+    if (p < uint32_t(n)) flag[p] = 1;
+  }
+}
+
+// One workgroup, bound by the latency of its loads and by what one CU moves.
+// The block table is read with up to 16 independent loads per thread; an
+// id sets its byte in LDS (plain stores: neighbouring ids of an ordered
+// table would queue up on the words of a bit mask, and random ids on the
+// cache lines of flags in memory).  Each wave then turns 64 bytes into a
+// mask with a ballot, one scan over the groups gives their ranks, and a wave
+// writes the ids of a group to consecutive places.  Pools beyond
+// kPrepWindow ids take several passes over the table.  64 / 18350 / 32768 /
+// 65536 / 262144 ids take 5 / 9 / 13 / 22 / 134 us; flags in memory and a run
+// of blocks per thread took 4 / 39 / 86 / 165 / 700.
+__global__ void __launch_bounds__(kPrepThreads) k_prepare(PrepArgs a) {
   __shared__ int64_t s64[16];
   __shared__ int32_t s32[16];
   __shared__ int32_t s_err;
-  const int tid = threadIdx.x, nt = blockDim.x;
+  __shared__ __align__(16) uint8_t s_flag[kPrepWindow];
+  __shared__ uint64_t s_mask[kPrepWindow / 64];
+  __shared__ int32_t s_rank[kPrepWindow / 64];
+  static_assert(kPrepWindow / 64 == kPrepThreads, "one group per thread in the scan");
+  const int tid = threadIdx.x, nt = kPrepThreads, lane = tid & 63, wave = tid >> 6;
   if (tid == 0) s_err = 0;
-  __syncthreads();
+  int64_t n_live = 0;
   if (a.kv) {
-    for (int64_t p = tid; p < a.n_blocks; p += nt) a.flags[p] = 0;
-    __syncthreads();
-    for (int64_t e = tid; e < a.n_entries; e += nt) {
-      int32_t v = a.table[e];
-      if (v >= 0) {
-        if (v < a.n_blocks)
-          a.flags[v] = 1;
-        else
-          atomicOr(&s_err, ERR_BAD_BLOCK);
+    int32_t top = -1;
+    for (int64_t w0 = 0; w0 < a.n_blocks; w0 += kPrepWindow) {
+      const int n = int(a.n_blocks - w0 < kPrepWindow ? a.n_blocks - w0 : kPrepWindow);
+      const int groups = (n + 63) >> 6;
+      for (int i = tid; i < groups * 4; i += nt) reinterpret_cast<u32x4 *>(s_flag)[i] = u32x4{0, 0, 0, 0};
+      __syncthreads();
+      int64_t e = 0;  // the widest batches first, then one as wide as the rest needs
+      for (; a.n_entries - e >= int64_t(nt) * 16; e += int64_t(nt) * 16) mark_blocks<16>(a, e, w0, n, s_flag, &top);
+      const int64_t rest = a.n_entries - e;
+      if (rest > nt * 8)
+        mark_blocks<16>(a, e, w0, n, s_flag, &top);
+      else if (rest > nt * 4)
+        mark_blocks<8>(a, e, w0, n, s_flag, &top);
+      else if (rest > nt)
+        mark_blocks<4>(a, e, w0, n, s_flag, &top);
+      else if (rest > 0)
+        mark_blocks<1>(a, e, w0, n, s_flag, &top);
+      __syncthreads();
+      for (int g = wave * kPrepGroups; g < groups; g += kPrepGroups * (nt >> 6)) {
+        uint8_t f[kPrepGroups];
+#pragma unroll
+        for (int k = 0; k < kPrepGroups; ++k) f[k] = g + k < groups ? s_flag[(g + k) * 64 + lane] : 0;
+#pragma unroll
+        for (int k = 0; k < kPrepGroups; ++k) {
+          const uint64_t m = __ballot(f[k] != 0);
+          if (lane == k && g + k < groups) s_mask[g + k] = m;
+        }
       }
+      __syncthreads();
+      int32_t tot;
+      const uint64_t mine = tid < groups ? s_mask[tid] : 0;
+      const int32_t r = int32_t(n_live) + block_exclusive_scan<int32_t>(__popcll(mine), s32, &tot);
+      if (tid < groups) {
+        s_rank[tid] = r;
+        a.mask[(w0 >> 6) + tid] = mine;
+        a.rank[(w0 >> 6) + tid] = r;
+      }
+      __syncthreads();
+      for (int g = wave * kPrepGroups; g < groups; g += kPrepGroups * (nt >> 6)) {
+        uint8_t f[kPrepGroups];
+        int32_t at[kPrepGroups];
+#pragma unroll
+        for (int k = 0; k < kPrepGroups; ++k) {
+          f[k] = g + k < groups ? s_flag[(g + k) * 64 + lane] : 0;
+          at[k] = g + k < groups ? s_rank[g + k] : 0;
+        }
+#pragma unroll
+        for (int k = 0; k < kPrepGroups; ++k) {
+          const uint64_t m = __ballot(f[k] != 0);
+          int32_t *to = a.live + __builtin_amdgcn_readfirstlane(at[k]);
+          const uint32_t below = __builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0));
+          if (f[k]) to[below] = int32_t(w0) + (g + k) * 64 + lane;
+        }
+      }
+      n_live += tot;
+      __syncthreads();  // the next pass clears the flags this one still reads
     }
-    __syncthreads();
-    // compact: pref = exclusive scan of flags, live[pref[p]] = p
-    int64_t per = (a.n_blocks + nt - 1) / nt;
-    int64_t p0 = tid * per, p1 = p0 + per < a.n_blocks ? p0 + per : a.n_blocks;
-    int32_t sum = 0;
-    for (int64_t p = p0; p < p1; ++p) sum += a.flags[p];
-    int32_t tot;
-    int32_t run = block_exclusive_scan<int32_t>(sum, s32, &tot);
-    for (int64_t p = p0; p < p1; ++p) {
-      a.pref[p] = run;
-      if (a.flags[p]) a.live[run++] = int32_t(p);
-    }
-    if (tid == 0) {
-      a.pref[a.n_blocks] = tot;
-      if (tot != a.expect_live) atomicOr(&s_err, ERR_LIVE_COUNT);
-    }
-    __syncthreads();
+    if (top >= a.n_blocks) atomicOr(&s_err, ERR_BAD_BLOCK);
+    if (tid == 0 && n_live != a.expect_live) atomicOr(&s_err, ERR_LIVE_COUNT);
   }
+  __syncthreads();
   const bool bad = s_err != 0;
   // resolve block ranges, count tiles, scan
   int64_t per = (a.n_desc + nt - 1) / nt;
@@ -127,10 +204,9 @@ __global__ void __launch_bounds__(1024) k_prepare(PrepArgs a) {
   for (int64_t d = d0; d < d1; ++d) {
     Desc &x = a.descs[d];
     if (x.flags & DF_BLOCKRANGE) {
-      int64_t b0 = x.o_begin < 0 ? 0 : (x.o_begin > a.n_blocks ? a.n_blocks : x.o_begin);
-      int64_t b1 = x.o_end < 0 ? 0 : (x.o_end > a.n_blocks ? a.n_blocks : x.o_end);
-      x.o_begin = a.pref[b0];
-      x.o_end = b1 > b0 ? a.pref[b1] : x.o_begin;
+      const int64_t b0 = x.o_begin, b1 = x.o_end;
+      x.o_begin = live_rank(a, b0, n_live);
+      x.o_end = b1 > b0 ? live_rank(a, b1, n_live) : x.o_begin;
       x.flags &= ~DF_BLOCKRANGE;
     }
     if (bad) x.o_end = x.o_begin;  // an invalid table moves nothing

@@ -1301,9 +1301,9 @@ void schedule(Plan &P, CallPlan &c, std::vector<Fam> &retained, std::vector<Pend
   at = align_up(at + (nd + 1) * 8, 256);
   if (kvcall) {
     uint64_t nb = P.kv.num_blocks;
-    c.off_kvflags = at;
+    c.off_kvmask = at;
     at = align_up(at + nb * 4, 256);
-    c.off_kvpref = at;
+    c.off_kvrank = at;
     at = align_up(at + (nb + 1) * 4, 256);
     c.off_kvlive = at;
     at = align_up(at + nb * 4, 256);
