@@ -1,6 +1,6 @@
 // exec.hip — executor of the reshard library (Sec. III-C physical stage on
-// one GPU): uploads the plan's descriptors into the caller's staging
-// buffer, launches the prepare and repack kernels level by level, lands the
+// one GPU): launches the prepare kernel (the plan's descriptors into the
+// caller's staging buffer) and the repack kernels level by level, lands the
 // missing bytes from the pinned host buffer (DMA copies of large contiguous
 // gaps straight into place; every other piece read by the copy kernel from
 // the host buffer, out of place beside the repack on a side stream that
@@ -721,7 +721,6 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
   char *host_out = static_cast<char *>(outbound_host);
   Desc *dev_desc = reinterpret_cast<Desc *>(b_st + c.off_desc);
   int64_t *dev_prefix = reinterpret_cast<int64_t *>(b_st + c.off_prefix);
-  int32_t *dev_err = reinterpret_cast<int32_t *>(b_st + c.off_meta);
   int32_t *dev_live = kvcall ? reinterpret_cast<int32_t *>(b_st + c.off_kvlive) : nullptr;
 
   Issuer is{E, cs, c, kvcall ? P.kv.num_blocks : 0, kvcall ? P.kv.live_blocks : 0, b_out, b_st, host_in,
@@ -757,15 +756,14 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
   if (!await)
     for (const HostCopy &h : c.directs) is.direct(h);
 
-  // ---- upload descriptors, prepare ----------------------------------------------
-  if (!c.fams.empty())
-    HIPCHK(hipMemcpyAsync(dev_desc, cs.desc_host, c.fams.size() * sizeof(Desc), hipMemcpyHostToDevice, compute));
+  // ---- prepare: descriptors into staging, block list, tile counts ------------------
   PrepArgs pa{};
+  pa.plan_descs = cs.desc_host;
   pa.descs = dev_desc;
   pa.n_desc = int32_t(c.fams.size());
   pa.kv = kvcall;
   pa.prefix = dev_prefix;
-  pa.err = dev_err;
+  pa.err = cs.err_host;
   if (kvcall) {
     pa.table = table;
     pa.n_entries = n_entries;
@@ -913,7 +911,6 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
   HIPCHK(hipEventRecord(cs.h2d1, copy));
 
   // ---- tails ----------------------------------------------------------------------
-  HIPCHK(hipMemcpyAsync(cs.err_host, dev_err, sizeof(int32_t), hipMemcpyDeviceToHost, compute));
   cs.tail_compute = E.ev_sync();
   HIPCHK(hipEventRecord(cs.tail_compute, compute));
   cs.tail_copy = E.ev_sync();

@@ -68,11 +68,12 @@ __device__ T block_exclusive_scan(T v, T *lds16, T *total) {
 }
 
 struct PrepArgs {
-  Desc *descs;
+  const Desc *plan_descs;  // the plan's descriptors, in pinned host memory
+  Desc *descs;             // their device copies, block ranges resolved
   int32_t n_desc;
   int32_t kv;            // 1: compact the block table first
   int64_t *prefix;       // [n_desc + 1] tile prefix
-  int32_t *err;          // error word (meta area)
+  int32_t *err;          // error word, in pinned host memory
   const int32_t *table;  // block table, n_entries int32
   int64_t n_entries;
   uint64_t *mask;        // [ceil(n_blocks / 64)] live blocks of each group of 64 ids
@@ -114,6 +115,12 @@ __device__ __forceinline__ void mark_blocks(const PrepArgs &a, int64_t e, int64_
 }
 
 // One workgroup, bound by the latency of its loads and by what one CU moves.
+// It reads the descriptors from the host's pinned copy and writes the error
+// word there itself: a copy command before it and one at the call's end cost
+// the stream a blit kernel each (2-4 us and the gaps beside them) and the
+// host two more calls; a TP 4->3 KV move of 84 MB took 87 us a call
+// with them and 83 without.
+//
 // The block table is read with up to 16 independent loads per thread; an
 // id sets its byte in LDS (plain stores: neighbouring ids of an ordered
 // table would queue up on the words of a bit mask, and random ids on the
@@ -133,6 +140,22 @@ __global__ void __launch_bounds__(kPrepThreads) k_prepare(PrepArgs a) {
   static_assert(kPrepWindow / 64 == kPrepThreads, "one group per thread in the scan");
   const int tid = threadIdx.x, nt = kPrepThreads, lane = tid & 63, wave = tid >> 6;
   if (tid == 0) s_err = 0;
+  // (the loops below read descs only after a barrier)
+  constexpr int kDescLoads = 4;
+  const int64_t words = int64_t(a.n_desc) * int64_t(sizeof(Desc) / 16);
+  for (int64_t i0 = tid; i0 < words; i0 += nt * kDescLoads) {
+    u32x4 v[kDescLoads];
+#pragma unroll
+    for (int k = 0; k < kDescLoads; ++k) {
+      const int64_t i = i0 + int64_t(k) * nt;
+      v[k] = reinterpret_cast<const u32x4 *>(a.plan_descs)[i < words ? i : words - 1];
+    }
+#pragma unroll
+    for (int k = 0; k < kDescLoads; ++k) {
+      const int64_t i = i0 + int64_t(k) * nt;
+      if (i < words) reinterpret_cast<u32x4 *>(a.descs)[i] = v[k];
+    }
+  }
   int64_t n_live = 0;
   if (a.kv) {
     int32_t top = -1;
@@ -225,6 +248,7 @@ __global__ void __launch_bounds__(kPrepThreads) k_prepare(PrepArgs a) {
   if (tid == 0) {
     a.prefix[a.n_desc] = tot;
     *a.err = s_err;
+    __threadfence_system();
   }
 }
 
