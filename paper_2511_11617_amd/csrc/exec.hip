@@ -58,7 +58,6 @@ struct CallState {
   Desc *desc_host = nullptr;  // pinned copy of the descriptors
   size_t desc_cap = 0;
   int32_t *err_host = nullptr;  // pinned error word
-  hipEvent_t start = nullptr;  // marks the caller's work queued before the call
   hipEvent_t tail_compute = nullptr, tail_copy = nullptr, tail_side = nullptr;
   hipEvent_t rep0 = nullptr, rep1 = nullptr, h2d0 = nullptr, h2d1 = nullptr, d2h0 = nullptr, d2h1 = nullptr;
   hipEvent_t hr1 = nullptr;  // end of the copy kernel's host reads (inflow ends with the later of h2d1, hr1)
@@ -66,6 +65,7 @@ struct CallState {
     int kind, level;
     uint64_t bytes;
     hipEvent_t e0, e1;
+    double ms = 0;  // once synced
   };
   std::vector<LaunchRec> launches;
   uint64_t h2d_bytes = 0, d2h_bytes = 0, scatter_bytes = 0, repack_bytes = 0;
@@ -440,10 +440,13 @@ void launch_copy(Exec &E, const Launch &L, const Desc *dev_desc, const int64_t *
 
 // ---- issuing one call ----------------------------------------------------------------
 // Every event recorded on a stream costs it a few microseconds (about 4.5 us
-// each on the MI355X, against 2 us between two bare launches), so the
-// launches of a stream share their timing marks: a launch that comes right
-// after a timed one starts at that launch's end mark, and the events other
-// streams wait on are those same marks.  mark[s] is the end mark of the last
+// each on the MI355X, against 2 us between two bare launches) and the host
+// as much, so the launches of a stream share their timing marks: a launch
+// that comes right after a timed one starts at that launch's end mark, and
+// the events other streams and atp_sync wait on are those same marks.  The
+// tiny TP 4->3 reshard took 155-175 us a step with a start, a tail and a
+// prepare event of their own on every stream, the copy stream's included
+// where nothing used it, and takes 104-115 us.  mark[s] is the end mark of the last
 // command queued on s when that command was a timed launch; other(s) forgets
 // it when anything else is queued there.  The Issuer also lands the inflow
 // pieces that are not repack: DMA copies of large gaps and the copy kernel's
@@ -469,7 +472,7 @@ struct Issuer {
   }
   template <class F>
   CallState::LaunchRec timed(int kind, int level, uint64_t bytes, hipStream_t st, const F &launch) {
-    CallState::LaunchRec r{kind, level, bytes, nullptr, E.ev_time()};
+    CallState::LaunchRec r{kind, level, bytes, nullptr, E.ev_time(), 0};
     auto it = mark.find(st);
     if (it != mark.end()) {
       r.e0 = it->second;
@@ -740,19 +743,19 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
 
   // every stream of this call starts after what the caller has queued on
   // `compute` when the call is made (with the other call of the plan
-  // pending, that includes the other call's work on `compute`)
-  cs.start = E.ev_sync();
+  // pending, that includes the other call's work on `compute`).  The copy
+  // stream is left alone when the call has no DMA landing for it.
+  const bool use_copy = !c.directs.empty() || !c.chunks.empty();
+  cs.h2d0 = E.ev_time();
   undo.enqueued = true;
-  HIPCHK(hipEventRecord(cs.start, compute));
-  HIPCHK(hipStreamWaitEvent(copy, cs.start, 0));
+  HIPCHK(hipEventRecord(cs.h2d0, compute));
+  if (use_copy) HIPCHK(hipStreamWaitEvent(copy, cs.h2d0, 0));
 
   // direct landings wait for nothing (the planner routes every landing that
   // would wait for a level or an outbound read elsewhere): they go first, so
   // that the link is busy at once.  While the inflow buffer is still being
   // filled (`await`) they go after the levels instead, with the host reads,
   // so that the host does not wait for the reads before the repack is queued.
-  cs.h2d0 = E.ev_time();
-  HIPCHK(hipEventRecord(cs.h2d0, copy));
   if (!await)
     for (const HostCopy &h : c.directs) is.direct(h);
 
@@ -777,11 +780,9 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
   hipLaunchKernelGGL(k_prepare, dim3(1), dim3(kPrepThreads), 0, compute, pa);
   HIPCHK(hipGetLastError());
   is.other(compute);
-  hipEvent_t prepared = nullptr;  // descriptors, prefix sums and live blocks in place
-  if (use_side) {
-    prepared = E.ev_sync();
-    is.record(prepared, compute);
-  }
+  // descriptors, prefix sums and live blocks in place: the side stream waits
+  // for this mark, and the first launch on `compute` starts at it
+  const hipEvent_t prepared = is.mark_or_record(compute, true);
 
   cs.hr1 = nullptr;
   // out of place: at once, on the side stream, beside the repack (the two
@@ -792,6 +793,7 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
     if (!await) {
       for (const Launch &L : c.host_reads) is.host_read(L, E.side);
       is.end_host_reads(E.side);
+      is.other(compute);  // the host was busy with these: the first level gets a start mark of its own
     }
   }
 
@@ -877,8 +879,7 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
       HIPCHK(hipMemcpyAsync(host_out + h.host_off, b_st + h.dev_off, h.bytes, hipMemcpyDeviceToHost, E.side));
       cs.d2h_bytes += h.bytes;
     }
-    cs.d2h1 = E.ev_time();
-    is.record(cs.d2h1, E.side);
+    cs.d2h1 = is.mark_or_record(E.side, true);
   }
 
   // ---- inflow ------------------------------------------------------------------------
@@ -907,42 +908,28 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
     }
     slot_free[i] = is.mark_or_record(late_comp, false);  // the chunk's last scatter is done
   }
-  cs.h2d1 = E.ev_time();  // the inflow ends with the later of this and hr1
-  HIPCHK(hipEventRecord(cs.h2d1, copy));
-
   // ---- tails ----------------------------------------------------------------------
-  cs.tail_compute = E.ev_sync();
-  HIPCHK(hipEventRecord(cs.tail_compute, compute));
-  cs.tail_copy = E.ev_sync();
-  HIPCHK(hipEventRecord(cs.tail_copy, copy));
-  cs.tail_side = nullptr;
-  if (use_side) {
+  // the last mark of each stream the call used; the inflow ends with the
+  // later of h2d1 and hr1
+  auto tails = [&E, &cs, compute, copy, use_copy, side = use_side ? E.side : hipStream_t(nullptr)](Issuer &is) {
+    cs.h2d1 = use_copy ? E.ev_time() : nullptr;
+    if (use_copy) HIPCHK(hipEventRecord(cs.h2d1, copy));
+    cs.tail_copy = cs.h2d1;
+    cs.tail_compute = is.mark_or_record(compute, false);
     // the side stream is not joined back into the caller's streams (that
     // would hold up the other call's work); atp_sync waits for it
-    cs.tail_side = E.ev_sync();
-    HIPCHK(hipEventRecord(cs.tail_side, E.side));
-  }
+    cs.tail_side = side ? is.mark_or_record(side, false) : nullptr;
+  };
+  tails(is);
   if (defer) {
     // the awaited pieces wait for the reads: atp_sync issues them (the
     // caller may queue the KV call meanwhile), then records the tails again
     auto d = std::make_shared<Issuer>(is);
     d->mark.clear();
     const std::function<void(uint64_t)> aw = *await;
-    const hipStream_t side = use_side ? E.side : nullptr;
-    cs.finish_issue = [d, aw, after_issue, await_stream, compute, copy, side]() {
-      Exec &E = d->E;
-      CallState &cs = d->cs;
+    cs.finish_issue = [d, aw, after_issue, await_stream, tails]() {
       d->awaited(await_stream, aw);
-      cs.h2d1 = E.ev_time();
-      HIPCHK(hipEventRecord(cs.h2d1, copy));
-      cs.tail_compute = E.ev_sync();
-      HIPCHK(hipEventRecord(cs.tail_compute, compute));
-      cs.tail_copy = E.ev_sync();
-      HIPCHK(hipEventRecord(cs.tail_copy, copy));
-      if (side) {
-        cs.tail_side = E.ev_sync();
-        HIPCHK(hipEventRecord(cs.tail_side, side));
-      }
+      tails(*d);
       if (after_issue) after_issue();
     };
   }
@@ -1007,8 +994,10 @@ int exec_sync(Plan &P, atp_timing *out) {
     }
     // busy time of the repack kernels (levels), and the span they cover
     double busy = 0;
-    for (const auto &L : cs.launches)
-      if (L.kind < 2) busy += ms(L.e0, L.e1);
+    for (auto &L : cs.launches) {
+      L.ms = ms(L.e0, L.e1);
+      if (L.kind < 2) busy += L.ms;
+    }
     (which == 0 ? t.repack_w_ms : t.repack_kv_ms) = busy;
     t.repack_span_ms += ms(cs.rep0, cs.rep1);
     rep_ms += busy;
@@ -1018,9 +1007,8 @@ int exec_sync(Plan &P, atp_timing *out) {
       if (e && (!h2d_last || ms(h2d_last, e) > 0)) h2d_last = e;
     t.d2h_ms = std::max(t.d2h_ms, ms(cs.d2h0, cs.d2h1));
     for (const auto &L : cs.launches) {
-      double m = ms(L.e0, L.e1);
-      if (L.kind == 2) t.scatter_ms += m;
-      E.last_launches.push_back({L.kind, L.level, L.bytes, m});
+      if (L.kind == 2) t.scatter_ms += L.ms;
+      E.last_launches.push_back({L.kind, L.level, L.bytes, L.ms});
     }
     t.repack_bytes += cs.repack_bytes;
     t.h2d_bytes += cs.h2d_bytes;
@@ -1036,7 +1024,10 @@ int exec_sync(Plan &P, atp_timing *out) {
     for (int which = 0; which < 2; ++which)
       if (was_pending[which])
         for (const auto &L : (which == 0 ? E.w : E.k).launches)
-          if (L.kind < 2 && L.e0 && L.e1) iv.push_back({ms(h2d_first, L.e0), ms(h2d_first, L.e1)});
+          if (L.kind < 2) {
+            const double at = ms(h2d_first, L.e0);
+            iv.push_back({at, at + L.ms});
+          }
     std::sort(iv.begin(), iv.end());
     double cur_lo = 0, cur_hi = 0;
     bool open = false;
