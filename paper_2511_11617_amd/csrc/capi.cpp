@@ -282,7 +282,7 @@ int atp_plan_copies(const atp_plan_t *plan, int32_t which, atp_copy *out, int32_
   for (const atp_copy &x : v) n_d2h += x.op == ATP_COPY_D2H && x.src_buf != ATP_BUF_STAGING;
   for (const atp::Launch &L : c.host_reads)
     for (int d = L.d0; d < L.d1; ++d) {
-      atp_copy x = dev_copy(c.fams[d], ATP_COPY_H2D, P.inplace && c.n_levels > 0 ? c.n_levels - 1 : -1);
+      atp_copy x = dev_copy(c.fams[d], ATP_COPY_H2D, L.gate);
       x.src_buf = ATP_BUF_INFLOW;
       x.after_d2h = n_d2h;
       v.push_back(x);

@@ -4,7 +4,8 @@
 // missing bytes from the pinned host buffer (DMA copies of large contiguous
 // gaps straight into place; every other piece read by the copy kernel from
 // the host buffer, out of place beside the repack on a side stream that
-// feeds a hardware queue of its own, in place after the last level; the
+// feeds a hardware queue of its own, in place beside the levels that no
+// longer read its destination, or after the last one; the
 // in-place KV inflow through the landing ring plus a scatter kernel), reads
 // dropped outbound bytes out before an in-place overwrite (the copy kernel
 // writing the host buffer, on the side stream), and orders all of it with
@@ -96,8 +97,9 @@ struct Exec {
   bool no_alloc = false;
   // In place: `side` runs the outbound gathers and their device-to-host
   // copies, the weight levels that wait for them and the weight inflow the
-  // copy kernel reads after them.  Out of place it runs the copy kernel's
-  // host reads.  It feeds another hardware queue than the caller's streams
+  // copy kernel reads after them, or without outbound reads the weight
+  // inflow beside the levels.  Out of place it runs the copy kernel's host
+  // reads.  It feeds another hardware queue than the caller's streams
   // and is shared process-wide (choose_side).
   hipStream_t side = nullptr;
   hipStream_t side_for_compute = nullptr, side_for_copy = nullptr;
@@ -738,7 +740,8 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
   // chosen before this call queues anything: the probe waits for what the
   // caller's streams already hold.
   const bool early_reads = !P.inplace && !c.host_reads.empty();
-  const bool use_side = do_out || early_reads;
+  const bool gated_reads = P.inplace && !do_out && !c.host_reads.empty() && !await;
+  const bool use_side = do_out || early_reads || gated_reads;
   if (use_side) choose_side(E, compute, copy);
 
   // every stream of this call starts after what the caller has queued on
@@ -840,6 +843,17 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
   // ---- repack levels ---------------------------------------------------------------
   hipEvent_t level0_end = nullptr;  // the KV outbound gathered at level 0 is copied out after it
   cs.rep0 = nullptr;
+  // in place without outbound reads, the host reads run on the side stream
+  // beside the levels, each launch once the levels up to its gate are done
+  size_t next_read = 0;
+  auto read_up_to = [&](int level) {
+    if (!gated_reads || next_read == c.host_reads.size() || c.host_reads[next_read].gate > level) return;
+    HIPCHK(hipStreamWaitEvent(E.side, is.mark_or_record(compute, true), 0));
+    is.other(E.side);
+    for (; next_read < c.host_reads.size() && c.host_reads[next_read].gate <= level; ++next_read)
+      is.host_read(c.host_reads[next_read], E.side);
+  };
+  read_up_to(-1);
   for (size_t i = 0; i < c.levels.size(); ++i) {
     const Launch &L = c.levels[i];
     if (split) {
@@ -853,18 +867,22 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
     if (!cs.rep0) cs.rep0 = r.e0;
     cs.repack_bytes += 2 * L.bytes;
     if (L.level == 0) level0_end = r.e1;
+    if (i + 1 == c.levels.size() || c.levels[i + 1].level != L.level) read_up_to(L.level);
   }
+  read_up_to(c.n_levels);
+  if (gated_reads) is.end_host_reads(E.side);
   if (split) issue_outbound(c.out_order.size());  // pieces no level waits for
   if (!cs.rep0) cs.rep0 = is.mark_or_record(late_comp, true);
   cs.rep1 = is.mark_or_record(late_comp, true);  // also: prepare and every level are done
 
-  // in place: the copy kernel reads every gated or strided inflow piece from
-  // the pinned host buffer into its final place, after the last level (and,
-  // for the weights, after every outbound read)
+  // in place with outbound reads (or with the inflow buffer still being
+  // filled): the copy kernel reads every gated or strided inflow piece from
+  // the pinned host buffer into its final place after the last level and
+  // every outbound read
   const hipStream_t await_stream = P.inplace ? late_comp : E.side;
   if (await && !defer) {
     is.awaited(await_stream, *await);
-  } else if (!await && P.inplace && !c.host_reads.empty()) {
+  } else if (!await && P.inplace && !gated_reads && !c.host_reads.empty()) {
     for (const Launch &L : c.host_reads) is.host_read(L, late_comp);
     is.end_host_reads(late_comp);
   }

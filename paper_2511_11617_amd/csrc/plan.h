@@ -64,6 +64,7 @@ struct Launch {
   uint64_t bytes = 0;  // bytes copied (upper bound for block ranges)
   uint64_t tiles_max = 0;
   std::vector<int> wait_outbound;  // outbound copies that must finish first
+  int gate = -1;  // host read: the level that must be done first (-1: none)
 };
 
 // Host <-> device copy of packed bytes.
@@ -98,7 +99,9 @@ struct CallPlan {
   std::vector<int> out_order;   // outbound issue order (by the level needing it)
   // Inflow other than large contiguous gaps is read by the copy kernel
   // straight from the pinned inflow buffer (host_reads): out of place from
-  // the call's start, in place after the call's last level.  In place, no
+  // the call's start; in place beside the levels, each launch after the
+  // level it is gated on, or after the last level where outbound reads gate
+  // it too.  In place, no
   // host-to-device copy command waits long for an event: such a command
   // holds up every later host-to-device copy of the process on the DMA
   // engine (the in-place KV inflow takes the landing ring, which waits only
