@@ -207,10 +207,9 @@ int atp_reshard_weights(atp_plan_t *plan, void *arena, uint64_t arena_bytes,
  * [n_seq][max_blocks], -1 = unused, read only; ids must be < num_blocks
  * and the distinct ids must number kv.live_blocks (else ATP_EINVAL from
  * atp_sync).  Buffers as for atp_reshard_weights, sizes from stats.*_kv.
- * With ATP_INPLACE the KV inflow lands only by DMA through the landing
- * ring (the copy kernel does not read it), so inflow_host may then be
- * ordinary pageable memory, at a lower copy rate; the outbound buffer must
- * still come from hipHostMalloc.
+ * With ATP_INPLACE inflow_host may be ordinary pageable memory: the KV
+ * inflow then lands by DMA through the landing ring, at a lower rate.  The
+ * outbound buffer must still come from hipHostMalloc.
  * The weights and KV calls may be pending together if their staging
  * buffers do not overlap; with ATP_INPLACE the weights call must then come
  * first (a weights call after a pending KV call is ATP_ESTATE). */
@@ -367,7 +366,10 @@ int atp_plan_launches(const atp_plan_t *plan, atp_launch *out, int32_t cap, int3
  *   REPACK   device copy of level `level`; all copies of one level run
  *            concurrently, levels run in order
  *   H2D_RING host inflow -> landing-ring slot (staging), then the SCATTER
- *            copies that follow it; ring traffic starts after all levels
+ *            copies that follow it, after all levels; where a slot takes
+ *            one H2D_RING copy and the inflow buffer is pinned, each
+ *            SCATTER reads that buffer instead, once level `level` has
+ *            finished (-1: at any time)
  *   H2D      host inflow -> arena, allowed once level `level` has
  *            finished (level -1: at any time) and the first `after_d2h`
  *            D2H copies of the list have finished

@@ -287,10 +287,12 @@ int atp_plan_copies(const atp_plan_t *plan, int32_t which, atp_copy *out, int32_
       x.after_d2h = n_d2h;
       v.push_back(x);
     }
+  std::vector<int> gate(c.fams.size(), -1);
+  for (const atp::Launch &L : c.chunk_reads) std::fill(gate.begin() + L.d0, gate.begin() + L.d1, L.gate);
   for (const atp::Chunk &ch : c.chunks) {
     for (const atp::HostCopy &h : ch.copies) v.push_back(host_copy(h, ATP_COPY_H2D_RING, -1, false));
     for (const atp::Launch &L : ch.scatters)
-      for (int d = L.d0; d < L.d1; ++d) v.push_back(dev_copy(c.fams[d], ATP_COPY_SCATTER, -1));
+      for (int d = L.d0; d < L.d1; ++d) v.push_back(dev_copy(c.fams[d], ATP_COPY_SCATTER, gate[size_t(d)]));
   }
   return copy_out(v, out, cap, n);
 }

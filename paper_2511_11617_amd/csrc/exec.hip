@@ -6,7 +6,8 @@
 // the host buffer, out of place beside the repack on a side stream that
 // feeds a hardware queue of its own, in place beside the levels that no
 // longer read its destination, or after the last one; the
-// in-place KV inflow through the landing ring plus a scatter kernel), reads
+// in-place KV inflow chunk by chunk, or from pageable memory through the
+// landing ring plus a scatter kernel), reads
 // dropped outbound bytes out before an in-place overwrite (the copy kernel
 // writing the host buffer, on the side stream), and orders all of it with
 // HIP events.
@@ -227,6 +228,14 @@ constexpr float kSpinMarginMs = 0.15f;   // the empty kernel must finish this mu
 #endif
 constexpr uint64_t kHostReadGrid = ATP_HOST_READ_GRID;
 constexpr uint64_t kOutboundGrid = 8;
+// Beside host reads by the kernel, the outbound writes share the link's
+// upstream direction with the reads' requests, and 8 workgroups of them slow
+// the reads: the 4-layer TP 8->7 reshard in place took 55.5 / 54.1 / 51.4 /
+// 51.1 ms a step with 16 / 8 / 5 / 4.  Four are enough where the KV inflow,
+// at kLinkRate, outlasts the outbound reads, at the kOutboundRate four
+// workgroups reach beside it (GB/s).
+constexpr uint64_t kOutboundGridBesideReads = 4;
+constexpr double kOutboundRate = 22, kLinkRate = 57;
 // host-read launch pieces while the inflow buffer is still being filled
 constexpr uint64_t kPipeBytes = 64ull << 20;
 std::map<std::pair<hipStream_t, hipStream_t>, bool> g_same_queue;  // under g_pool_mu
@@ -312,22 +321,29 @@ void choose_side(Exec &E, hipStream_t compute, hipStream_t copy) {
 }
 
 // The copy kernel reads or writes a host buffer only through its device
-// address; memory not pinned by HIP would fault the GPU, so it is refused.
-void check_kernel_host_buffer(const void *p, uint64_t bytes, const char *what) {
-  if (!bytes) return;
-  if (!p) throw Error(ATP_EINVAL, std::string(what) + " is NULL");
-  if (reinterpret_cast<uintptr_t>(p) % 256)
-    throw Error(ATP_EALIGN, std::string(what) + " must be 256-byte aligned (the copy kernel accesses it directly)");
+// address: memory not pinned by HIP would fault the GPU.
+bool kernel_readable(const void *p, uint64_t bytes) {
+  if (!p || !bytes || reinterpret_cast<uintptr_t>(p) % 256) return false;
   for (const char *q : {static_cast<const char *>(p), static_cast<const char *>(p) + bytes - 1}) {
     hipPointerAttribute_t a{};
     if (hipPointerGetAttributes(&a, q) != hipSuccess || a.type != hipMemoryTypeHost || a.hostPointer == nullptr ||
         a.devicePointer != a.hostPointer) {
       (void)hipGetLastError();
-      throw Error(ATP_EINVAL, std::string(what) +
-                                  " must be pinned host memory from hipHostMalloc "
-                                  "(the copy kernel accesses it directly)");
+      return false;
     }
   }
+  return true;
+}
+
+void check_kernel_host_buffer(const void *p, uint64_t bytes, const char *what) {
+  if (!bytes) return;
+  if (!p) throw Error(ATP_EINVAL, std::string(what) + " is NULL");
+  if (reinterpret_cast<uintptr_t>(p) % 256)
+    throw Error(ATP_EALIGN, std::string(what) + " must be 256-byte aligned (the copy kernel accesses it directly)");
+  if (!kernel_readable(p, bytes))
+    throw Error(ATP_EINVAL, std::string(what) +
+                                " must be pinned host memory from hipHostMalloc "
+                                "(the copy kernel accesses it directly)");
 }
 
 void build_descs(Exec &E, const CallPlan &c, CallState &cs) {
@@ -503,12 +519,24 @@ struct Issuer {
   void direct(const HostCopy &h) {
     HIPCHK(hipMemcpyAsync(b_out + h.dev_off, host_in + h.host_off, h.bytes, hipMemcpyHostToDevice, copy));
     cs.h2d_bytes += h.bytes;
+    other(copy);
   }
   // the copy kernel reads inflow pieces from the pinned host buffer into
   // their final place (kind 4 launches)
   void host_read(const Launch &L, hipStream_t s) {
     timed(4, -1, L.bytes, s, [&] {
       launch_copy(E, L, dev_desc, dev_prefix, const_cast<char *>(host_in), b_out, b_st, dev_live, s, kHostReadGrid);
+    });
+    cs.h2d_bytes += L.bytes;
+  }
+  // a landing-ring chunk read the same way: its scatter's descriptors address
+  // the slot, so the base moves until the slot's bytes are the chunk's bytes
+  // of the inflow buffer
+  void chunk_read(const Launch &L, const HostCopy &h, hipStream_t s) {
+    char *base = reinterpret_cast<char *>(reinterpret_cast<uintptr_t>(host_in) + h.host_off - h.dev_off);
+    timed(4, -1, L.bytes, s, [&] {
+      launch_copy(E, L, dev_desc, dev_prefix, nullptr, b_out, base, dev_live, s,
+                  L.wide ? kHostReadGrid * kUnroll / kWideUnroll : kHostReadGrid);
     });
     cs.h2d_bytes += L.bytes;
   }
@@ -669,6 +697,19 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
             throw Error(ATP_EINVAL, std::string(what) + ": an arena or staging buffer overlaps one of the pending " +
                                         (kvcall ? "weights" : "kv") + " call");
   }
+  // A landing-ring chunk (the in-place KV inflow) is read by the copy kernel
+  // straight from the inflow buffer where that is pinned, beside the levels:
+  // its scatter reads the packed bytes of its one copy at their place in the
+  // buffer instead of in the slot.  It needs no copy command, no slot and no second pass over
+  // the bytes, and it does not depend on which DMA engine the runtime gives
+  // the copy stream: the ring's copies ran at 57 GB/s in some processes and
+  // at 30 in others, for all of a process's passes after the first, so that
+  // the 4-layer TP 8->7 reshard in place took 52.1 ms a step or 81.9; read
+  // by the kernel it takes 51.4 (80 layers: 1017 -> 1008).
+  const bool ring_pinned = !c.chunks.empty() && kernel_readable(inflow_host, inflow_bytes);
+  auto read_from_host = [ring_pinned](const Chunk &ch) {
+    return ring_pinned && ch.copies.size() == 1 && ch.copies[0].host_off % 16 == ch.copies[0].dev_off % 16;
+  };
   if (!c.host_reads.empty()) check_kernel_host_buffer(inflow_host, inflow_bytes, "inflow buffer");
   if (do_out && c.out_d0 >= 0) check_kernel_host_buffer(outbound_host, c.outbound_bytes, "outbound buffer");
 
@@ -796,7 +837,7 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
     if (!await) {
       for (const Launch &L : c.host_reads) is.host_read(L, E.side);
       is.end_host_reads(E.side);
-      is.other(compute);  // the host was busy with these: the first level gets a start mark of its own
+      is.other(compute);  // the first level gets a start mark of its own, as below
     }
   }
 
@@ -808,6 +849,8 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
   // That work and the weight inflow read after it stay off the caller's
   // streams, so that they do not hold up the other call's work queued
   // behind them.
+  const uint64_t out_grid = double(P.k.inflow) * kOutboundRate >= double(c.outbound_bytes) * kLinkRate
+                                ? kOutboundGridBesideReads : kOutboundGrid;
   size_t issued = 0;  // outbound pieces read out so far, in plan order
   const bool split = do_out && !kvcall;
   hipStream_t late_comp = compute;
@@ -831,7 +874,7 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
       }
       L.d1 = c.out_d0 + int(issued);
       const CallState::LaunchRec r = is.timed(3, -1, L.bytes, late_comp, [&] {
-        launch_copy(E, L, dev_desc, dev_prefix, b_in, host_out, b_st, dev_live, late_comp, kOutboundGrid);
+        launch_copy(E, L, dev_desc, dev_prefix, b_in, host_out, b_st, dev_live, late_comp, out_grid);
       });
       if (!cs.d2h0) cs.d2h0 = r.e0;
       cs.d2h1 = r.e1;
@@ -843,15 +886,30 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
   // ---- repack levels ---------------------------------------------------------------
   hipEvent_t level0_end = nullptr;  // the KV outbound gathered at level 0 is copied out after it
   cs.rep0 = nullptr;
-  // in place without outbound reads, the host reads run on the side stream
-  // beside the levels, each launch once the levels up to its gate are done
-  size_t next_read = 0;
+  // In place, the host reads run beside the levels, each launch once the
+  // levels up to its gate are done: the weights' on the side stream (with
+  // outbound reads they follow those instead), the KV chunks' on the copy
+  // stream, which nothing else of the call needs then.
+  size_t next_read = 0, next_chunk = 0;
+  auto due = [](const std::vector<Launch> &v, size_t i, int level) { return i < v.size() && v[i].gate <= level; };
   auto read_up_to = [&](int level) {
-    if (!gated_reads || next_read == c.host_reads.size() || c.host_reads[next_read].gate > level) return;
-    HIPCHK(hipStreamWaitEvent(E.side, is.mark_or_record(compute, true), 0));
-    is.other(E.side);
-    for (; next_read < c.host_reads.size() && c.host_reads[next_read].gate <= level; ++next_read)
-      is.host_read(c.host_reads[next_read], E.side);
+    const size_t before = next_read + next_chunk;
+    if (gated_reads && due(c.host_reads, next_read, level)) {
+      HIPCHK(hipStreamWaitEvent(E.side, is.mark_or_record(compute, true), 0));
+      is.other(E.side);
+      for (; due(c.host_reads, next_read, level); ++next_read) is.host_read(c.host_reads[next_read], E.side);
+    }
+    if (ring_pinned && due(c.chunk_reads, next_chunk, level)) {
+      HIPCHK(hipStreamWaitEvent(copy, is.mark_or_record(compute, true), 0));
+      is.other(copy);
+      for (; due(c.chunk_reads, next_chunk, level); ++next_chunk) {
+        const Launch &L = c.chunk_reads[next_chunk];
+        const Chunk &ch = c.chunks[size_t(L.chunk)];
+        if (read_from_host(ch)) is.chunk_read(L, ch.copies[0], copy);
+      }
+    }
+    // the host was busy with these: the first level gets a start mark of its own
+    if (level < 0 && next_read + next_chunk > before) is.other(compute);
   };
   read_up_to(-1);
   for (size_t i = 0; i < c.levels.size(); ++i) {
@@ -871,6 +929,7 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
   }
   read_up_to(c.n_levels);
   if (gated_reads) is.end_host_reads(E.side);
+  if (ring_pinned) is.end_host_reads(copy);
   if (split) issue_outbound(c.out_order.size());  // pieces no level waits for
   if (!cs.rep0) cs.rep0 = is.mark_or_record(late_comp, true);
   cs.rep1 = is.mark_or_record(late_comp, true);  // also: prepare and every level are done
@@ -903,14 +962,15 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
   // ---- inflow ------------------------------------------------------------------------
   // (direct landings went first, none of them waits for anything; the copy
   // kernel's host reads are issued above)
-  // ring (the in-place KV call only): H2D into a slot, then a scatter from it
-  // after every level; a chunk reuses its slot once the slot's previous
-  // scatter is done
-  std::vector<hipEvent_t> slot_free(c.chunks.size(), nullptr);
-  for (size_t i = 0; i < c.chunks.size(); ++i) {
-    const Chunk &ch = c.chunks[i];
-    if (i >= size_t(c.n_slots) && slot_free[i - c.n_slots])
-      HIPCHK(hipStreamWaitEvent(copy, slot_free[i - c.n_slots], 0));
+  // the in-place KV call's chunks that the copy kernel did not read above go
+  // through the ring: H2D into a slot (once the slot's previous scatter is
+  // done), then a scatter from it after every level
+  std::vector<hipEvent_t> slot_free(size_t(c.n_slots), nullptr);
+  for (const Chunk &ch : c.chunks) {
+    if (read_from_host(ch)) continue;
+    is.other(copy);
+    hipEvent_t &free = slot_free[size_t(ch.slot)];
+    if (free) HIPCHK(hipStreamWaitEvent(copy, free, 0));
     for (const HostCopy &h : ch.copies) {
       HIPCHK(hipMemcpyAsync(b_st + h.dev_off, host_in + h.host_off, h.bytes, hipMemcpyHostToDevice, copy));
       cs.h2d_bytes += h.bytes;
@@ -924,15 +984,14 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
                [&] { launch_copy(E, L, dev_desc, dev_prefix, b_in, b_out, b_st, dev_live, late_comp); });
       cs.scatter_bytes += L.bytes;
     }
-    slot_free[i] = is.mark_or_record(late_comp, false);  // the chunk's last scatter is done
+    free = is.mark_or_record(late_comp, false);  // the chunk's last scatter is done
   }
+
   // ---- tails ----------------------------------------------------------------------
   // the last mark of each stream the call used; the inflow ends with the
   // later of h2d1 and hr1
   auto tails = [&E, &cs, compute, copy, use_copy, side = use_side ? E.side : hipStream_t(nullptr)](Issuer &is) {
-    cs.h2d1 = use_copy ? E.ev_time() : nullptr;
-    if (use_copy) HIPCHK(hipEventRecord(cs.h2d1, copy));
-    cs.tail_copy = cs.h2d1;
+    cs.tail_copy = cs.h2d1 = use_copy ? is.mark_or_record(copy, true) : nullptr;
     cs.tail_compute = is.mark_or_record(compute, false);
     // the side stream is not joined back into the caller's streams (that
     // would hold up the other call's work); atp_sync waits for it

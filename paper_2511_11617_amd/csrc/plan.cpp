@@ -759,7 +759,7 @@ void emit_group(CallPlan &c, std::vector<Fam> group, int level, int kind, std::v
   for (Fam &f : group) {
     f.flags &= ~(DF_ALIGNED | DF_WIDE | DF_SRC_GRID);
     if (!fam_aligned(f)) {
-      if (kind == 4) f.flags |= DF_SRC_GRID;  // reads of the pinned host buffer
+      if (kind == 4 || kind == 2) f.flags |= DF_SRC_GRID;  // reads of the pinned host buffer
       continue;
     }
     f.flags |= DF_ALIGNED;
@@ -1209,6 +1209,18 @@ void schedule(Plan &P, CallPlan &c, std::vector<Fam> &retained, std::vector<Pend
       max_item = std::max<uint64_t>(max_item, f.rows * f.run);
     }
   }
+  // the last level that reads bytes of `d` (-1: none does)
+  auto read_gate = [&](Span d) {
+    int gate = -1;
+    if (P.inplace)
+      ridx.query(d, [&](int a) { gate = std::max(gate, nodes[a].kind == Node::NORMAL ? nodes[a].level : 0); });
+    return gate;
+  };
+  // whether reads of `bytes` that wait for levels up to `gate` become a
+  // launch, or are merged with those of the next gate
+  auto reads_due = [&](uint64_t bytes, bool first, int gate) {
+    return bytes >= (first ? kReadFirst : kReadMin) || gate + 1 >= c.n_levels;
+  };
   // host reads keep the narrow tile: more bytes in flight over PCIe would
   // slow the repack beside them
   auto emit_reads = [&](const std::vector<Fam> &group, int gate) {
@@ -1227,12 +1239,7 @@ void schedule(Plan &P, CallPlan &c, std::vector<Fam> &retained, std::vector<Pend
     // over the link, 12 levels of 0.38 ms) the step took 1.75 ms with every
     // read after the last level and 1.48 ms with gates.
     std::vector<std::vector<Fam>> by_gate(size_t(c.n_levels) + 1);
-    for (const Fam &f : host_pieces) {
-      int gate = -1;
-      ridx.query(dst_span(f, f.o_begin, f.o_end),
-                 [&](int a) { gate = std::max(gate, nodes[a].kind == Node::NORMAL ? nodes[a].level : 0); });
-      by_gate[size_t(gate + 1)].push_back(f);
-    }
+    for (const Fam &f : host_pieces) by_gate[size_t(read_gate(dst_span(f, f.o_begin, f.o_end)) + 1)].push_back(f);
     std::vector<Fam> group;
     uint64_t bytes = 0;
     for (int gate = -1; gate < c.n_levels; ++gate) {
@@ -1240,7 +1247,7 @@ void schedule(Plan &P, CallPlan &c, std::vector<Fam> &retained, std::vector<Pend
         group.push_back(f);
         bytes += f.bytes();
       }
-      if (bytes < (c.host_reads.empty() ? kReadFirst : kReadMin) && gate + 1 < c.n_levels) continue;
+      if (!reads_due(bytes, c.host_reads.empty(), gate)) continue;
       emit_reads(group, gate);
       group.clear();
       bytes = 0;
@@ -1323,6 +1330,55 @@ void schedule(Plan &P, CallPlan &c, std::vector<Fam> &retained, std::vector<Pend
       }
     }
     flush();
+  }
+
+  // The chunks' pieces as host reads (where the inflow buffer turns out to be
+  // pinned): a piece may land once the last level that reads its plane is
+  // done, so the upper planes of a growing cache, which land beyond the old
+  // ones, start at once.
+  if (!c.chunks.empty()) {
+    struct Unit {
+      int chunk, d;
+      const Launch *L;
+    };
+    std::vector<std::vector<Unit>> by_gate(size_t(c.n_levels) + 1);
+    for (size_t i = 0; i < c.chunks.size(); ++i)
+      for (const Launch &L : c.chunks[i].scatters)
+        for (int d = L.d0; d < L.d1; ++d) {
+          const Fam &f = c.fams[size_t(d)];
+          // an indexed piece may touch any block of its plane
+          const int64_t last = (f.flags & DF_DST_IND) ? P.kv.num_blocks - 1 : f.o_end - f.o_begin - 1;
+          const Span w{f.dst_off, f.dst_off + uint64_t(last) * f.dst_ostride + (f.rows - 1) * f.dst_pitch + f.run};
+          by_gate[size_t(read_gate(w) + 1)].push_back({int(i), d, &L});
+        }
+    std::vector<Unit> group;
+    uint64_t bytes = 0;
+    for (int gate = -1; gate < c.n_levels; ++gate) {
+      for (const Unit &u : by_gate[size_t(gate + 1)]) {
+        group.push_back(u);
+        bytes += c.fams[size_t(u.d)].bytes();
+      }
+      if (!reads_due(bytes, c.chunk_reads.empty(), gate)) continue;
+      std::sort(group.begin(), group.end(), [](const Unit &x, const Unit &y) { return x.d < y.d; });
+      for (const Unit &u : group) {
+        const bool joins = !c.chunk_reads.empty() && c.chunk_reads.back().gate == gate &&
+                           c.chunk_reads.back().chunk == u.chunk && c.chunk_reads.back().d1 == u.d &&
+                           u.d != u.L->d0;
+        if (!joins) {
+          Launch L = *u.L;
+          L.kind = 4;
+          L.gate = gate;
+          L.chunk = u.chunk;
+          L.d0 = u.d;
+          L.bytes = 0;
+          c.chunk_reads.push_back(L);
+        }
+        c.chunk_reads.back().d1 = u.d + 1;
+        c.chunk_reads.back().bytes += c.fams[size_t(u.d)].bytes();
+      }
+      group.clear();
+      bytes = 0;
+    }
   }
 
   // ---- staging layout ------------------------------------------------------------------

@@ -65,6 +65,7 @@ struct Launch {
   uint64_t tiles_max = 0;
   std::vector<int> wait_outbound;  // outbound copies that must finish first
   int gate = -1;  // host read: the level that must be done first (-1: none)
+  int chunk = -1; // host read of a landing-ring chunk
 };
 
 // Host <-> device copy of packed bytes.
@@ -95,6 +96,9 @@ struct CallPlan {
   std::vector<Launch> levels;   // repack launches in order
   std::vector<HostCopy> directs;
   std::vector<Chunk> chunks;
+  // the chunks' scatters once more, as launches that read the pinned inflow
+  // buffer beside the levels instead, in the order of their gates
+  std::vector<Launch> chunk_reads;
   std::vector<HostCopy> outbound;
   std::vector<int> out_order;   // outbound issue order (by the level needing it)
   // Inflow other than large contiguous gaps is read by the copy kernel
