@@ -17,6 +17,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "desc.h"
 
 namespace atp {
@@ -274,13 +276,12 @@ struct LineAddr {
 // cache (constant address space) instead of a per-lane vector load.
 typedef const int32_t __attribute__((address_space(4))) *const_i32_p;
 
-// Addresses of line `line` of descriptor x.  UNIFORM: `line` is the same on
-// every lane of the wave, and the block id comes in through a scalar load.
+// Addresses of the first line of outer item `orel` of descriptor x.
+// UNIFORM: `orel` is the same on every lane of the wave, and the block id
+// comes in through a scalar load.
 template <bool UNIFORM>
-__device__ __forceinline__ LineAddr line_addr(const Desc &x, uint32_t line, char *b0, char *b1, char *b2,
+__device__ __forceinline__ LineAddr item_addr(const Desc &x, uint32_t orel, char *b0, char *b1, char *b2,
                                               const int32_t *__restrict__ live) {
-  uint32_t orel = divq(line, x.magic_rows);
-  uint32_t r = line - orel * x.rows;
   int64_t o = x.o_begin + orel;
   uint64_t id = 0;
   if (x.flags & (DF_SRC_IND | DF_DST_IND))
@@ -290,8 +291,20 @@ __device__ __forceinline__ LineAddr line_addr(const Desc &x, uint32_t line, char
   char *sb = slot_base((x.flags >> DF_SRC_SHIFT) & 3, b0, b1, b2);
   char *db = slot_base((x.flags >> DF_DST_SHIFT) & 3, b0, b1, b2);
   LineAddr la;
-  la.src = sb + x.src_off + si * x.src_ostride + uint64_t(r) * x.src_pitch;
-  la.dst = db + x.dst_off + di * x.dst_ostride + uint64_t(r) * x.dst_pitch;
+  la.src = sb + x.src_off + si * x.src_ostride;
+  la.dst = db + x.dst_off + di * x.dst_ostride;
+  return la;
+}
+
+// Addresses of line `line` of descriptor x.
+template <bool UNIFORM>
+__device__ __forceinline__ LineAddr line_addr(const Desc &x, uint32_t line, char *b0, char *b1, char *b2,
+                                              const int32_t *__restrict__ live) {
+  const uint32_t orel = divq(line, x.magic_rows);
+  const uint32_t r = line - orel * x.rows;
+  LineAddr la = item_addr<UNIFORM>(x, orel, b0, b1, b2, live);
+  la.src += uint64_t(r) * x.src_pitch;
+  la.dst += uint64_t(r) * x.dst_pitch;
   return la;
 }
 
@@ -327,6 +340,56 @@ __device__ __forceinline__ int64_t tile_of_block() {
 #else
   return blockIdx.x;
 #endif
+}
+
+// Source and destination of this thread's U chunks of a tile, for lines of
+// any alignment (ANY) or aligned ones.  The line is resolved once per
+// wavefront when its 64 chunks share one (KV head runs), else the outer item
+// when they share that (the tokens of a block in the token-major layout:
+// with a block id per lane, each chunk waited for its id before its load:
+// host reads of 268 MB into 256 B lines took 4.97 ms, now 4.78),
+// else per lane.  Lanes past the tile's end get its last chunk.
+template <int U, bool ANY>
+__device__ __forceinline__ void tile_addr(const Desc &x, uint64_t cbase, uint64_t clast, char *b0, char *b1, char *b2,
+                                          const int32_t *__restrict__ live, const char **sp, char **dp) {
+  // an aligned descriptor has fewer than 2^32 chunks
+  using C = typename std::conditional<ANY, uint64_t, uint32_t>::type;
+  const C base = C(cbase), last = C(clast);
+  const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+#pragma unroll
+  for (int k = 0; k < U; ++k) {
+    const C g0r = base + k * kThreads + wv * 64;
+    const C g0 = g0r < last ? g0r : last;
+    const C gl = last - g0 > 63 ? g0 + 63 : last;
+    const C cr = base + k * kThreads + threadIdx.x;
+    const C c = cr < last ? cr : last;
+    const uint32_t lf = divl(g0, x.magic_line), ll = divl(gl, x.magic_line);
+    LineAddr la;
+    uint32_t col;
+    if (lf == ll) {
+      la = line_addr<true>(x, lf, b0, b1, b2, live);
+      col = uint32_t(c - C(lf) * x.cpl);
+    } else {
+      const uint32_t line = divl(c, x.magic_line);
+      const uint32_t item = divq(lf, x.magic_rows);
+      if (item == divq(ll, x.magic_rows)) {
+        la = item_addr<true>(x, item, b0, b1, b2, live);
+        la.src += uint64_t(line - item * x.rows) * x.src_pitch;
+        la.dst += uint64_t(line - item * x.rows) * x.dst_pitch;
+      } else {
+        la = line_addr<false>(x, line, b0, b1, b2, live);
+      }
+      col = uint32_t(c - C(line) * x.cpl);
+    }
+    int32_t off = int32_t(col * 16);
+    if (ANY) {
+      const uint32_t h = uint32_t(uintptr_t((x.flags & DF_SRC_GRID) ? la.src : la.dst)) & 15;
+      const int32_t o = off - int32_t(h), omax = int32_t(x.run) - 16;
+      off = o < 0 ? 0 : (o > omax ? omax : o);
+    }
+    sp[k] = la.src + off;
+    dp[k] = la.dst + off;
+  }
 }
 
 // Each tile resolves every address first (descriptor by value, block ids
@@ -370,37 +433,15 @@ __global__ void __launch_bounds__(kThreads) k_copy16(const Desc *__restrict__ de
       }
       continue;
     }
-    // several lines per tile: resolve the line once per wavefront when its
-    // 64 chunks share one (short KV head runs), else per lane
-    const u32x4 *sp[U];
-    u32x4 *dp[U];
-    const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // several lines per tile
+    const char *sp[U];
+    char *dp[U];
+    tile_addr<U, false>(x, cbase, clast, b0, b1, b2, live, sp, dp);
 #pragma unroll
-    for (int k = 0; k < U; ++k) {
-      const uint64_t g0r = cbase + uint64_t(k) * kThreads + wv * 64;
-      const uint64_t g0 = g0r < clast ? g0r : clast;
-      const uint64_t gl = g0r + 63 < clast ? g0r + 63 : clast;
-      const uint64_t cr = cbase + threadIdx.x + uint64_t(k) * kThreads;
-      const uint64_t c = cr < clast ? cr : clast;
-      const uint32_t lf = divq(uint32_t(g0), x.magic_line);
-      if (lf == divq(uint32_t(gl), x.magic_line)) {
-        const LineAddr la = line_addr<true>(x, lf, b0, b1, b2, live);
-        const uint32_t col = uint32_t(c) - lf * cpl;
-        sp[k] = reinterpret_cast<const u32x4 *>(la.src) + col;
-        dp[k] = reinterpret_cast<u32x4 *>(la.dst) + col;
-      } else {
-        const uint32_t line = divq(uint32_t(c), x.magic_line);
-        const uint32_t col = uint32_t(c) - line * cpl;
-        const LineAddr la = line_addr<false>(x, line, b0, b1, b2, live);
-        sp[k] = reinterpret_cast<const u32x4 *>(la.src) + col;
-        dp[k] = reinterpret_cast<u32x4 *>(la.dst) + col;
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < U; ++k) v[k] = load16(sp[k]);
+    for (int k = 0; k < U; ++k) v[k] = load16(reinterpret_cast<const u32x4 *>(sp[k]));
 #pragma unroll
     for (int k = 0; k < U; ++k)
-      if (cbase + threadIdx.x + uint64_t(k) * kThreads <= clast) store16(dp[k], v[k]);
+      if (cbase + threadIdx.x + uint64_t(k) * kThreads <= clast) store16(reinterpret_cast<u32x4 *>(dp[k]), v[k]);
   }
 }
 
@@ -429,12 +470,20 @@ __device__ __forceinline__ void store16_any(char *p, u32x4 v) {
   __builtin_nontemporal_store(v, (global_u32x4_any *)(p));
 }
 
+// Lines [c0, c1] shorter than one chunk, one per lane, byte by byte.
+__device__ __forceinline__ void copy_short_lines(const Desc &x, uint64_t c0, uint64_t c1, char *b0, char *b1, char *b2,
+                                                 const int32_t *__restrict__ live) {
+  for (uint64_t c = c0 + threadIdx.x; c <= c1; c += kThreads) {
+    const LineAddr la = line_addr<false>(x, uint32_t(c), b0, b1, b2, live);
+    for (uint32_t i = 0; i < x.run; ++i) ((global_u8 *)la.dst)[i] = ((const global_u8 *)la.src)[i];
+  }
+}
+
 __global__ void __launch_bounds__(kThreads) k_copy_any(const Desc *__restrict__ descs,
                                                        const int64_t *__restrict__ prefix, int d0, int d1, char *b0,
                                                        char *b1, char *b2, const int32_t *__restrict__ live) {
   constexpr int U = kUnroll;
   const int64_t T0 = prefix[d0], T1 = prefix[d1];
-  const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   for (int64_t t = T0 + tile_of_block(); t < T1; t += gridDim.x) {
     const int d = find_desc(prefix, d0, d1, t);
     const Desc x = descs[d];
@@ -442,38 +491,12 @@ __global__ void __launch_bounds__(kThreads) k_copy_any(const Desc *__restrict__ 
     const uint64_t cbase = uint64_t(t - prefix[d]) * kTileChunks;
     const uint64_t clast = (cbase + kTileChunks < total ? cbase + kTileChunks : total) - 1;
     if (x.run < 16) {
-      for (uint64_t c = cbase + threadIdx.x; c <= clast; c += kThreads) {
-        const LineAddr la = line_addr<false>(x, uint32_t(c), b0, b1, b2, live);
-        for (uint32_t i = 0; i < x.run; ++i) ((global_u8 *)la.dst)[i] = ((const global_u8 *)la.src)[i];
-      }
+      copy_short_lines(x, cbase, clast, b0, b1, b2, live);
       continue;
     }
     const char *sp[U];
     char *dp[U];
-#pragma unroll
-    for (int k = 0; k < U; ++k) {
-      const uint64_t g0r = cbase + uint64_t(k) * kThreads + wv * 64;
-      const uint64_t g0 = g0r < clast ? g0r : clast;
-      const uint64_t gl = g0r + 63 < clast ? g0r + 63 : clast;
-      const uint64_t cr = cbase + threadIdx.x + uint64_t(k) * kThreads;
-      const uint64_t c = cr < clast ? cr : clast;
-      const uint32_t lf = divl(g0, x.magic_line);
-      LineAddr la;
-      uint32_t col;
-      if (lf == divl(gl, x.magic_line)) {
-        la = line_addr<true>(x, lf, b0, b1, b2, live);
-        col = uint32_t(c - uint64_t(lf) * x.cpl);
-      } else {
-        const uint32_t line = divl(c, x.magic_line);
-        la = line_addr<false>(x, line, b0, b1, b2, live);
-        col = uint32_t(c - uint64_t(line) * x.cpl);
-      }
-      const uint32_t h = uint32_t(uintptr_t((x.flags & DF_SRC_GRID) ? la.src : la.dst)) & 15;
-      const int32_t o = int32_t(col * 16) - int32_t(h), omax = int32_t(x.run) - 16;
-      const int32_t off = o < 0 ? 0 : (o > omax ? omax : o);
-      sp[k] = la.src + off;
-      dp[k] = la.dst + off;
-    }
+    tile_addr<U, true>(x, cbase, clast, b0, b1, b2, live, sp, dp);
     u32x4 v[U];
 #pragma unroll
     for (int k = 0; k < U; ++k) v[k] = load16_any(sp[k]);
