@@ -35,13 +35,9 @@ enum : uint32_t {
 };
 
 // Launch shape of the vector kernel: 256 threads, ATP_UNROLL independent
-// 16-byte chunks per thread per tile; one workgroup per tile unless
-// ATP_PERSIST (grid-stride over tiles with a fixed grid).
+// 16-byte chunks per thread per tile; one workgroup per tile.
 #ifndef ATP_UNROLL
 #define ATP_UNROLL 2
-#endif
-#ifndef ATP_PERSIST
-#define ATP_PERSIST 0
 #endif
 #ifndef ATP_NT_LOAD
 #define ATP_NT_LOAD 1

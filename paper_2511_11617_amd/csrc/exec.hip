@@ -91,7 +91,6 @@ std::map<int, DevicePool> g_pools;
 
 struct Exec {
   int device = -1;
-  int grid_max = 2048;
   // Set while a call of the no-allocation entry point is being issued:
   // events, pinned buffers and the side stream then come from the pools
   // atp_warmup filled, and running short is an error, not an allocation.
@@ -185,9 +184,6 @@ Exec &exec_of(Plan &P) {
   if (!P.exec) {
     Exec *e = new Exec();
     HIPCHK(hipGetDevice(&e->device));
-    int cus = 0;
-    HIPCHK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, e->device));
-    e->grid_max = std::max(1, cus) * 8;
     P.exec = e;
   }
   return *static_cast<Exec *>(P.exec);
@@ -212,30 +208,6 @@ __global__ void k_nop() {}
 constexpr uint32_t kSpinIters = 100;     // about 0.34 ms at 2.4 GHz
 constexpr float kSpinMarginMs = 0.15f;   // the empty kernel must finish this much earlier
 
-// Workgroups of the launches that move bytes over PCIe with the copy kernel
-// (persistent grids over their tiles).  Host reads: 32 workgroups carry a
-// full x16 Gen5 link from pinned host memory (57 GB/s; 16 reach 50).  The
-// long-latency host reads they keep in flight slow an HBM-bound repack
-// running beside them, the more the wider the grid: the 40-layer TP 4->3
-// repack ran at 6.14 / 5.97 / 5.55 / 2.63 / 1.12 TB/s beside 32 / 48 / 64 /
-// 80 / 128 host-read workgroups (6.2 alone).  The outbound reads get a narrow
-// grid: wide device-to-host writers (the runtime's 512-workgroup blits)
-// slowed a concurrent HBM-bound repack several-fold; 8 workgroups leave a
-// concurrent HBM copy at full speed while writing 17 GB/s beside it (41 GB/s
-// alone).
-#ifndef ATP_HOST_READ_GRID
-#define ATP_HOST_READ_GRID 32
-#endif
-constexpr uint64_t kHostReadGrid = ATP_HOST_READ_GRID;
-constexpr uint64_t kOutboundGrid = 8;
-// Beside host reads by the kernel, the outbound writes share the link's
-// upstream direction with the reads' requests, and 8 workgroups of them slow
-// the reads: the 4-layer TP 8->7 reshard in place took 55.5 / 54.1 / 51.4 /
-// 51.1 ms a step with 16 / 8 / 5 / 4.  Four are enough where the KV inflow,
-// at kLinkRate, outlasts the outbound reads, at the kOutboundRate four
-// workgroups reach beside it (GB/s).
-constexpr uint64_t kOutboundGridBesideReads = 4;
-constexpr double kOutboundRate = 22, kLinkRate = 57;
 // host-read launch pieces while the inflow buffer is still being filled
 constexpr uint64_t kPipeBytes = 64ull << 20;
 std::map<std::pair<hipStream_t, hipStream_t>, bool> g_same_queue;  // under g_pool_mu
@@ -438,21 +410,62 @@ void check_extents(const CallPlan &c, bool kvcall, const Plan &P, uint64_t in_by
       throw Error(ATP_EINVAL, "internal: an outbound read has the wrong shape");
 }
 
-void launch_copy(Exec &E, const Launch &L, const Desc *dev_desc, const int64_t *dev_prefix, char *b0, char *b1,
-                 char *b2, const int32_t *live, hipStream_t s, uint64_t grid_cap = 0) {
-  // one workgroup per tile, or a fixed persistent grid (the kernels loop
-  // over the tiles of the launch)
-  uint64_t cap = grid_cap ? grid_cap : ATP_PERSIST ? uint64_t(E.grid_max) : (uint64_t(1) << 30);
-  uint64_t g = std::min<uint64_t>(std::max<uint64_t>(L.tiles_max, 1), cap);
-  if (L.aligned && L.wide)
-    hipLaunchKernelGGL((k_copy16<kWideUnroll>), dim3(unsigned(g)), dim3(kThreads), 0, s, dev_desc, dev_prefix, L.d0,
-                       L.d1, b0, b1, b2, live);
-  else if (L.aligned)
-    hipLaunchKernelGGL((k_copy16<kUnroll>), dim3(unsigned(g)), dim3(kThreads), 0, s, dev_desc, dev_prefix, L.d0,
-                       L.d1, b0, b1, b2, live);
+// Workgroups of a launch over the link: aligned, with two tiles in flight
+// (k_copy_link) or one (k_copy16); aligned with wide tiles (k_copy_link);
+// unaligned (k_copy_any, one tile).
+struct LinkGrid {
+  uint64_t narrow, wide, any;
+  bool two;
+};
+
+// Workgroups of the launches that move bytes over PCIe with the copy kernels
+// (persistent grids over their tiles).  Host reads: about 256 KiB in flight
+// carry a full x16 Gen5 link from pinned host memory (57 GB/s; half of it 50).
+// The long-latency host reads they keep in flight slow an HBM-bound repack
+// running beside them, the more the wider the grid: the 40-layer TP 4->3
+// repack ran at 6.14 / 5.97 / 5.55 / 2.63 / 1.12 TB/s beside 32 / 48 / 64 / 80
+// / 128 workgroups with one tile (6.2 alone).
+constexpr LinkGrid kHostRead = {32, 10, 32, false};
+// Two tiles in flight keep the rate up while a repack runs beside the reads,
+// and lose a little where none does.  ms a step with one tile on 32
+// workgroups and two on 14 / 16 / 18 / 20 / 24 / 32:
+//   40-layer TP 8->7, last rank    7.37   6.74 6.67 6.68 6.65 6.63 6.67
+//   4-layer TP 4->3 (repack 3 %)  12.22  12.38 12.42 12.31 12.39 12.76 12.62
+// so two are used where the repack (kRepackRate, GB/s read and written) lasts
+// at least a quarter of the reads' time: in place, where the levels of the
+// 8-layer TP 8->7 last rank last 0.3 of it with their gaps and 0.16 without,
+// one tile was 0.8 % ahead.
+constexpr LinkGrid kHostReadBesideRepack = {20, 10, 32, true};
+constexpr double kRepackRate = 6000;
+// The outbound reads get a narrow grid: wide device-to-host writers (the
+// runtime's 512-workgroup blits) slowed a concurrent HBM-bound repack
+// several-fold; 64 KiB in flight leave a concurrent HBM copy at full speed
+// while writing 17 GB/s beside it (51 GB/s alone; with one tile on 8
+// workgroups 45, two tiles on 3 / 6 / 8 workgroups 40 / 44 / 48).
+constexpr LinkGrid kOutbound = {4, 2, 8, true};
+// Beside host reads, the outbound writes share the link's upstream direction
+// with the reads' requests and slow the reads: the 4-layer TP 8->7 reshard in
+// place took 55.5 / 54.1 / 51.4 / 51.1 ms a step with 16 / 8 / 5 / 4 workgroups
+// of one tile.  Half of kOutbound is enough where the KV inflow, at kLinkRate,
+// outlasts the outbound reads, at the kOutboundRate they reach beside it (GB/s).
+constexpr LinkGrid kOutboundBesideReads = {2, 1, 4, true};
+constexpr double kOutboundRate = 22, kLinkRate = 57;
+
+void launch_copy(const Launch &L, const Desc *dev_desc, const int64_t *dev_prefix, char *b0, char *b1, char *b2,
+                 const int32_t *live, hipStream_t s, const LinkGrid *link = nullptr) {
+  // one workgroup per tile, or a narrow persistent grid over the link (the
+  // kernels loop over the tiles of the launch)
+  const uint64_t cap = !link ? uint64_t(1) << 30 : !L.aligned ? link->any : L.wide ? link->wide : link->narrow;
+  const dim3 g(unsigned(std::min<uint64_t>(std::max<uint64_t>(L.tiles_max, 1), cap)));
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, g, dim3(kThreads), 0, s, dev_desc, dev_prefix, L.d0, L.d1, b0, b1, b2, live);
+  };
+  if (!L.aligned)
+    go(k_copy_any);
+  else if (link && (L.wide || link->two))
+    L.wide ? go(k_copy_link<kWideUnroll>) : go(k_copy_link<kUnroll>);
   else
-    hipLaunchKernelGGL(k_copy_any, dim3(unsigned(g)), dim3(kThreads), 0, s, dev_desc, dev_prefix, L.d0, L.d1, b0,
-                       b1, b2, live);
+    L.wide ? go(k_copy16<kWideUnroll>) : go(k_copy16<kUnroll>);
   HIPCHK(hipGetLastError());
 }
 
@@ -477,6 +490,7 @@ struct Issuer {
   int64_t nb, live;  // KV pool size and live blocks (0 for the weights call)
   char *b_out, *b_st;
   const char *host_in;
+  const LinkGrid &read_grid;
   Desc *dev_desc;
   int64_t *dev_prefix;
   int32_t *dev_live;
@@ -525,7 +539,7 @@ struct Issuer {
   // their final place (kind 4 launches)
   void host_read(const Launch &L, hipStream_t s) {
     timed(4, -1, L.bytes, s, [&] {
-      launch_copy(E, L, dev_desc, dev_prefix, const_cast<char *>(host_in), b_out, b_st, dev_live, s, kHostReadGrid);
+      launch_copy(L, dev_desc, dev_prefix, const_cast<char *>(host_in), b_out, b_st, dev_live, s, &read_grid);
     });
     cs.h2d_bytes += L.bytes;
   }
@@ -535,8 +549,7 @@ struct Issuer {
   void chunk_read(const Launch &L, const HostCopy &h, hipStream_t s) {
     char *base = reinterpret_cast<char *>(reinterpret_cast<uintptr_t>(host_in) + h.host_off - h.dev_off);
     timed(4, -1, L.bytes, s, [&] {
-      launch_copy(E, L, dev_desc, dev_prefix, nullptr, b_out, base, dev_live, s,
-                  L.wide ? kHostReadGrid * kUnroll / kWideUnroll : kHostReadGrid);
+      launch_copy(L, dev_desc, dev_prefix, nullptr, b_out, base, dev_live, s, &read_grid);
     });
     cs.h2d_bytes += L.bytes;
   }
@@ -769,7 +782,10 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
   int64_t *dev_prefix = reinterpret_cast<int64_t *>(b_st + c.off_prefix);
   int32_t *dev_live = kvcall ? reinterpret_cast<int32_t *>(b_st + c.off_kvlive) : nullptr;
 
-  Issuer is{E, cs, c, kvcall ? P.kv.num_blocks : 0, kvcall ? P.kv.live_blocks : 0, b_out, b_st, host_in,
+  const double repack = 2 * double(P.w.moved + P.k.moved) / kRepackRate,
+               reads = double(P.w.inflow + P.k.inflow) / kLinkRate;
+  const LinkGrid &read_grid = repack >= 0.25 * reads ? kHostReadBesideRepack : kHostRead;
+  Issuer is{E, cs, c, kvcall ? P.kv.num_blocks : 0, kvcall ? P.kv.live_blocks : 0, b_out, b_st, host_in, read_grid,
             dev_desc, dev_prefix, dev_live, copy, {}};
   cs.compute = compute;
   cs.copy = copy;
@@ -849,8 +865,8 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
   // That work and the weight inflow read after it stay off the caller's
   // streams, so that they do not hold up the other call's work queued
   // behind them.
-  const uint64_t out_grid = double(P.k.inflow) * kOutboundRate >= double(c.outbound_bytes) * kLinkRate
-                                ? kOutboundGridBesideReads : kOutboundGrid;
+  const LinkGrid &out_grid = double(P.k.inflow) * kOutboundRate >= double(c.outbound_bytes) * kLinkRate
+                                 ? kOutboundBesideReads : kOutbound;
   size_t issued = 0;  // outbound pieces read out so far, in plan order
   const bool split = do_out && !kvcall;
   hipStream_t late_comp = compute;
@@ -874,7 +890,7 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
       }
       L.d1 = c.out_d0 + int(issued);
       const CallState::LaunchRec r = is.timed(3, -1, L.bytes, late_comp, [&] {
-        launch_copy(E, L, dev_desc, dev_prefix, b_in, host_out, b_st, dev_live, late_comp, out_grid);
+        launch_copy(L, dev_desc, dev_prefix, b_in, host_out, b_st, dev_live, late_comp, &out_grid);
       });
       if (!cs.d2h0) cs.d2h0 = r.e0;
       cs.d2h1 = r.e1;
@@ -920,7 +936,7 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
       issue_outbound(need);
     }
     const CallState::LaunchRec r = is.timed(kvcall ? 1 : 0, L.level, L.bytes, late_comp, [&] {
-      launch_copy(E, L, dev_desc, dev_prefix, b_in, b_out, b_st, dev_live, late_comp);
+      launch_copy(L, dev_desc, dev_prefix, b_in, b_out, b_st, dev_live, late_comp);
     });
     if (!cs.rep0) cs.rep0 = r.e0;
     cs.repack_bytes += 2 * L.bytes;
@@ -981,7 +997,7 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
     is.other(late_comp);
     for (const Launch &L : ch.scatters) {
       is.timed(2, -1, L.bytes, late_comp,
-               [&] { launch_copy(E, L, dev_desc, dev_prefix, b_in, b_out, b_st, dev_live, late_comp); });
+               [&] { launch_copy(L, dev_desc, dev_prefix, b_in, b_out, b_st, dev_live, late_comp); });
       cs.scatter_bytes += L.bytes;
     }
     free = is.mark_or_record(late_comp, false);  // the chunk's last scatter is done
@@ -1159,6 +1175,8 @@ void exec_warmup(void *compute_, void *copy_, int events) {
   Exec E;  // hands its events back to the device pool when it goes
   HIPCHK(hipGetDevice(&E.device));
   hipFuncAttributes fa;
+  HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy_link<kUnroll>)));
+  HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy_link<kWideUnroll>)));
   HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy16<kUnroll>)));
   HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy16<kWideUnroll>)));
   HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy_any)));
