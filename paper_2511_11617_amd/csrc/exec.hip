@@ -806,10 +806,12 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
   // pending, that includes the other call's work on `compute`).  The copy
   // stream is left alone when the call has no DMA landing for it.
   const bool use_copy = !c.directs.empty() || !c.chunks.empty();
-  cs.h2d0 = E.ev_time();
   undo.enqueued = true;
-  HIPCHK(hipEventRecord(cs.h2d0, compute));
-  if (use_copy) HIPCHK(hipStreamWaitEvent(copy, cs.h2d0, 0));
+  if (use_copy) {
+    cs.h2d0 = E.ev_time();
+    HIPCHK(hipEventRecord(cs.h2d0, compute));
+    HIPCHK(hipStreamWaitEvent(copy, cs.h2d0, 0));
+  }
 
   // direct landings wait for nothing (the planner routes every landing that
   // would wait for a level or an outbound read elsewhere): they go first, so
@@ -843,6 +845,7 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
   // descriptors, prefix sums and live blocks in place: the side stream waits
   // for this mark, and the first launch on `compute` starts at it
   const hipEvent_t prepared = is.mark_or_record(compute, true);
+  if (!use_copy) cs.h2d0 = prepared;  // nothing of the inflow starts before it
 
   cs.hr1 = nullptr;
   // out of place: at once, on the side stream, beside the repack (the two

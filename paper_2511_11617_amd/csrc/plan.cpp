@@ -750,21 +750,39 @@ uint64_t fam_tiles(const Fam &f, int64_t items_hint) {
   return (chunks + uint64_t(tile_chunks(f.flags)) - 1) / uint64_t(tile_chunks(f.flags));
 }
 
+// Most aligned bytes that join the launch of a group's unaligned ones.  A
+// launch costs its stream 6-7 us and the host as much; k_copy_any copies
+// aligned lines about 20 % slower than k_copy16 (over HBM; over the link
+// equally fast), 1 us at 8 MiB.  The tiny TP 4->3 reshard took 98-116 us a step
+// with two launches for each of its mixed groups and takes 79-89.
+constexpr uint64_t kJoinMax = 8ull << 20;
+
 // Emit launches for a group of families: aligned ones first (with wide
 // tiles, if `allow_wide`, for short KV lines), then the ones that are not.
 // Families are appended to c.fams; every family of a launch has the same
 // DF_ALIGNED and DF_WIDE flags.
 void emit_group(CallPlan &c, std::vector<Fam> group, int level, int kind, std::vector<Launch> &out,
                 int64_t live_hint, bool allow_wide) {
+  bool mixed = false;
+  uint64_t narrow = 0;
   for (Fam &f : group) {
     f.flags &= ~(DF_ALIGNED | DF_WIDE | DF_SRC_GRID);
     if (!fam_aligned(f)) {
-      if (kind == 4 || kind == 2) f.flags |= DF_SRC_GRID;  // reads of the pinned host buffer
+      mixed = true;
       continue;
     }
     f.flags |= DF_ALIGNED;
     if (allow_wide && f.run <= kWideMaxRun && (f.flags & (DF_SRC_IND | DF_DST_IND | DF_BLOCKRANGE)))
       f.flags |= DF_WIDE;
+    else
+      narrow += uint64_t(std::min<int64_t>(f.o_end - f.o_begin, live_hint)) * f.rows * f.run;
+  }
+  // the unaligned kernel copies aligned families too: few bytes of them join
+  // its launch
+  mixed = mixed && narrow <= kJoinMax;
+  for (Fam &f : group) {
+    if (mixed && !(f.flags & DF_WIDE)) f.flags &= ~DF_ALIGNED;
+    if (!(f.flags & DF_ALIGNED) && (kind == 4 || kind == 2)) f.flags |= DF_SRC_GRID;  // the pinned host buffer
   }
   for (int pass = 0; pass < 3; ++pass) {
     Launch L;
@@ -1118,6 +1136,9 @@ void schedule(Plan &P, CallPlan &c, std::vector<Fam> &retained, std::vector<Pend
     // the copy kernel reads them out: arena (slot IN) -> pinned outbound
     // buffer (slot OUT of those launches), packed row after row
     c.out_d0 = int(c.fams.size());
+    std::vector<Fam> pieces;
+    uint64_t bytes = 0;
+    int runs = 0;
     for (int o : c.out_order) {
       const HostCopy &h = c.outbound[size_t(o)];
       Fam f;
@@ -1130,9 +1151,17 @@ void schedule(Plan &P, CallPlan &c, std::vector<Fam> &retained, std::vector<Pend
       f.run = h.run;
       f.rows = 1;
       f.flags = bufs(BUF_IN, BUF_OUT);
-      const bool al = fam_aligned(f);
-      if (al) f.flags |= DF_ALIGNED;
-      c.out_aligned.push_back(al);
+      if (fam_aligned(f)) f.flags |= DF_ALIGNED;
+      runs += pieces.empty() || (f.flags & DF_ALIGNED) != (pieces.back().flags & DF_ALIGNED);
+      bytes += f.bytes();
+      pieces.push_back(f);
+    }
+    // a launch takes a run of pieces of one alignment: where the runs are
+    // short, all of them are left to the unaligned kernel (45 against 51 GB/s)
+    const bool join = runs > 1 && bytes <= uint64_t(runs) * kJoinMax;
+    for (Fam &f : pieces) {
+      if (join) f.flags &= ~DF_ALIGNED;
+      c.out_aligned.push_back((f.flags & DF_ALIGNED) != 0);
       c.out_tiles.push_back(fam_tiles(f, f.o_end));
       c.fams.push_back(f);
     }
