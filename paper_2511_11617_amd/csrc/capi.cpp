@@ -276,15 +276,13 @@ int atp_plan_copies(const atp_plan_t *plan, int32_t which, atp_copy *out, int32_
     v.push_back(x);
   }
   // inflow the copy kernel reads from the host buffer: in place after the
-  // last level and after every outbound read of the call, out of place at
+  // level and the outbound reads that read its destination, out of place at
   // any time
-  int32_t n_d2h = 0;
-  for (const atp_copy &x : v) n_d2h += x.op == ATP_COPY_D2H && x.src_buf != ATP_BUF_STAGING;
   for (const atp::Launch &L : c.host_reads)
     for (int d = L.d0; d < L.d1; ++d) {
       atp_copy x = dev_copy(c.fams[d], ATP_COPY_H2D, L.gate);
       x.src_buf = ATP_BUF_INFLOW;
-      x.after_d2h = n_d2h;
+      x.after_d2h = L.outs;
       v.push_back(x);
     }
   std::vector<int> gate(c.fams.size(), -1);

@@ -60,7 +60,7 @@ struct CallState {
   Desc *desc_host = nullptr;  // pinned copy of the descriptors
   size_t desc_cap = 0;
   int32_t *err_host = nullptr;  // pinned error word
-  hipEvent_t tail_compute = nullptr, tail_copy = nullptr, tail_side = nullptr;
+  hipEvent_t tail_compute = nullptr, tail_copy = nullptr, tail_side = nullptr, tail_reads = nullptr;
   hipEvent_t rep0 = nullptr, rep1 = nullptr, h2d0 = nullptr, h2d1 = nullptr, d2h0 = nullptr, d2h1 = nullptr;
   hipEvent_t hr1 = nullptr;  // end of the copy kernel's host reads (inflow ends with the later of h2d1, hr1)
   struct LaunchRec {
@@ -103,6 +103,9 @@ struct Exec {
   // and is shared process-wide (choose_side).
   hipStream_t side = nullptr;
   hipStream_t side_for_compute = nullptr, side_for_copy = nullptr;
+  // In place with outbound reads: the weight inflow beside them, on one more
+  // queue; null where none is free (the reads then follow on `side`).
+  hipStream_t reads = nullptr;
   std::vector<hipEvent_t> sync_pool, time_pool;
   size_t sync_used = 0, time_used = 0;
   CallState w, k;
@@ -246,50 +249,76 @@ bool same_queue(Exec &E, hipStream_t a, hipStream_t b) {
 constexpr size_t kSideStreams = 8;
 std::map<std::tuple<int, hipStream_t, hipStream_t>, hipStream_t> g_side;  // under g_pool_mu
 
-void choose_side(Exec &E, hipStream_t compute, hipStream_t copy) {
-  if (E.side && E.side_for_compute == compute && E.side_for_copy == copy) return;
-  const auto key = std::make_tuple(E.device, compute, copy);
+std::map<std::tuple<int, hipStream_t, hipStream_t>, hipStream_t> g_reads;  // likewise Exec::reads
+
+// A stream of the device's side streams on a hardware queue that none of
+// `busy` uses, or null.
+hipStream_t free_queue_stream(Exec &E, std::initializer_list<hipStream_t> busy) {
   std::vector<hipStream_t> known;
   {
     std::lock_guard<std::mutex> g(g_pool_mu);
-    auto it = g_side.find(key);
-    if (it != g_side.end()) {
-      E.side = it->second;
-      E.side_for_compute = compute;
-      E.side_for_copy = copy;
-      return;
-    }
     known = g_pools[E.device].streams;
   }
-  hipStream_t pick = nullptr;
-  for (size_t i = 0; !pick; ++i) {
+  for (size_t i = 0; i < std::max(known.size(), kSideStreams); ++i) {
     hipStream_t s = nullptr;
     if (i < known.size()) {
       s = known[i];
-    } else if (i < kSideStreams) {
+    } else {
       if (E.no_alloc)
         throw Error(ATP_ESTATE, "no side stream chosen for these streams: call atp_warmup(compute, copy) first");
       HIPCHK(hipStreamCreateWithFlags(&s, hipStreamNonBlocking));  // default priority
       std::lock_guard<std::mutex> g(g_pool_mu);
       g_pools[E.device].streams.push_back(s);
-      known.push_back(s);
-    } else {
-      break;
     }
-    if (!same_queue(E, compute, s) && !same_queue(E, copy, s)) pick = s;
+    bool free = true;
+    for (hipStream_t b : busy) free = free && !same_queue(E, b, s);
+    if (free) return s;
   }
-  if (!pick) {
-    if (known.empty()) throw Error(ATP_EHIP, "no stream for the in-place outbound work");
-    pick = known.front();
-    fprintf(stderr, "atp: no hardware queue free of the caller's streams among %zu streams; the in-place "
-                    "outbound work shares one\n", known.size());
-  }
-  {
+  return nullptr;
+}
+
+void choose_side(Exec &E, hipStream_t compute, hipStream_t copy) {
+  if (E.side && E.side_for_compute == compute && E.side_for_copy == copy) return;
+  const auto key = std::make_tuple(E.device, compute, copy);
+  auto find = [&] {
     std::lock_guard<std::mutex> g(g_pool_mu);
-    E.side = g_side.insert({key, pick}).first->second;  // another thread may have chosen first
+    auto it = g_side.find(key);
+    return it == g_side.end() ? hipStream_t(nullptr) : it->second;
+  };
+  hipStream_t pick = find();
+  if (!pick) {
+    pick = free_queue_stream(E, {compute, copy});
+    std::lock_guard<std::mutex> g(g_pool_mu);
+    if (!pick) {
+      const auto &known = g_pools[E.device].streams;
+      if (known.empty()) throw Error(ATP_EHIP, "no stream for the in-place outbound work");
+      pick = known.front();
+      fprintf(stderr, "atp: no hardware queue free of the caller's streams among %zu streams; the in-place "
+                      "outbound work shares one\n", known.size());
+    }
+    pick = g_side.insert({key, pick}).first->second;  // another thread may have chosen first
   }
+  E.side = pick;
   E.side_for_compute = compute;
   E.side_for_copy = copy;
+  E.reads = nullptr;
+}
+
+// After choose_side.
+void choose_reads(Exec &E) {
+  if (E.reads) return;
+  const auto key = std::make_tuple(E.device, E.side_for_compute, E.side_for_copy);
+  {
+    std::lock_guard<std::mutex> g(g_pool_mu);
+    auto it = g_reads.find(key);
+    if (it != g_reads.end()) {
+      E.reads = it->second;
+      return;
+    }
+  }
+  const hipStream_t pick = free_queue_stream(E, {E.side_for_compute, E.side_for_copy, E.side});
+  std::lock_guard<std::mutex> g(g_pool_mu);
+  E.reads = g_reads.insert({key, pick}).first->second;
 }
 
 // The copy kernel reads or writes a host buffer only through its device
@@ -450,6 +479,12 @@ constexpr LinkGrid kOutbound = {4, 2, 8, true};
 // outlasts the outbound reads, at the kOutboundRate they reach beside it (GB/s).
 constexpr LinkGrid kOutboundBesideReads = {2, 1, 4, true};
 constexpr double kOutboundRate = 22, kLinkRate = 57;
+// The weight inflow read beside kOutbound: fewer reads in flight leave the
+// writes more of the upstream direction.  ms for the weights of the 4-layer
+// 80-layer-shape TP 8->7 share in place (721 MB in, 587 MB out) with 12 / 16
+// / 20 / 24 / 32 workgroups: 20.3 / 18.5 / 17.9 / 17.9 / 19.8 beside 4
+// outbound workgroups, 21.9 / 19.8 / 19.5 / 19.3 / 19.0 beside 6.
+constexpr LinkGrid kHostReadBesideOutbound = {24, 10, 24, false};
 
 void launch_copy(const Launch &L, const Desc *dev_desc, const int64_t *dev_prefix, char *b0, char *b1, char *b2,
                  const int32_t *live, hipStream_t s, const LinkGrid *link = nullptr) {
@@ -746,7 +781,7 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
       E.no_alloc = false;
       if (!armed) return;
       if (enqueued)
-        for (hipStream_t s : {s0, s1, E.side})
+        for (hipStream_t s : {s0, s1, E.side, E.reads})
           if (s && hipStreamSynchronize(s) != hipSuccess) (void)hipGetLastError();
       release_scratch(E, cs);
     }
@@ -782,9 +817,11 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
   int64_t *dev_prefix = reinterpret_cast<int64_t *>(b_st + c.off_prefix);
   int32_t *dev_live = kvcall ? reinterpret_cast<int32_t *>(b_st + c.off_kvlive) : nullptr;
 
-  const double repack = 2 * double(P.w.moved + P.k.moved) / kRepackRate,
-               reads = double(P.w.inflow + P.k.inflow) / kLinkRate;
-  const LinkGrid &read_grid = repack >= 0.25 * reads ? kHostReadBesideRepack : kHostRead;
+  const double t_repack = 2 * double(P.w.moved + P.k.moved) / kRepackRate,
+               t_reads = double(P.w.inflow + P.k.inflow) / kLinkRate;
+  const LinkGrid &read_grid = do_out && !kvcall && !await       ? kHostReadBesideOutbound
+                              : t_repack >= 0.25 * t_reads ? kHostReadBesideRepack
+                                                           : kHostRead;
   Issuer is{E, cs, c, kvcall ? P.kv.num_blocks : 0, kvcall ? P.kv.live_blocks : 0, b_out, b_st, host_in, read_grid,
             dev_desc, dev_prefix, dev_live, copy, {}};
   cs.compute = compute;
@@ -797,9 +834,13 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
   // chosen before this call queues anything: the probe waits for what the
   // caller's streams already hold.
   const bool early_reads = !P.inplace && !c.host_reads.empty();
-  const bool gated_reads = P.inplace && !do_out && !c.host_reads.empty() && !await;
-  const bool use_side = do_out || early_reads || gated_reads;
+  const bool inplace_reads = P.inplace && !c.host_reads.empty() && !await;
+  const bool use_side = do_out || early_reads || inplace_reads;
   if (use_side) choose_side(E, compute, copy);
+  if (inplace_reads && do_out) choose_reads(E);
+  // in place, the stream that reads beside the levels: null where only a
+  // queue of its own would do and none is free
+  const hipStream_t reads = inplace_reads ? (do_out ? E.reads : E.side) : nullptr;
 
   // every stream of this call starts after what the caller has queued on
   // `compute` when the call is made (with the other call of the plan
@@ -880,14 +921,52 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
   }
   std::vector<size_t> pos_of(c.outbound.size(), 0);
   for (size_t p = 0; p < c.out_order.size(); ++p) pos_of[size_t(c.out_order[p])] = p;
+  cs.d2h0 = cs.d2h1 = nullptr;
+
+  // ---- repack levels ---------------------------------------------------------------
+  hipEvent_t level0_end = nullptr;  // the KV outbound gathered at level 0 is copied out after it
+  cs.rep0 = nullptr;
+  // In place, the host reads run beside the levels and the outbound reads,
+  // each launch once those up to its gate are done: the weights' on the side
+  // stream or, where that runs outbound reads and levels, on one of their
+  // own, the KV chunks' on the copy stream, which nothing else of the call
+  // needs then.
+  size_t next_read = 0, next_chunk = 0;
+  int level_done = -1;
+  auto due = [&](const std::vector<Launch> &v, size_t i) {
+    return i < v.size() && v[i].gate <= level_done && size_t(v[i].outs) <= issued;
+  };
+  auto issue_reads = [&] {
+    const size_t before = next_read + next_chunk;
+    if (reads && due(c.host_reads, next_read)) {
+      HIPCHK(hipStreamWaitEvent(reads, is.mark_or_record(late_comp, true), 0));
+      is.other(reads);
+      for (; due(c.host_reads, next_read); ++next_read) is.host_read(c.host_reads[next_read], reads);
+    }
+    if (ring_pinned && due(c.chunk_reads, next_chunk)) {
+      HIPCHK(hipStreamWaitEvent(copy, is.mark_or_record(compute, true), 0));
+      is.other(copy);
+      for (; due(c.chunk_reads, next_chunk); ++next_chunk) {
+        const Launch &L = c.chunk_reads[next_chunk];
+        const Chunk &ch = c.chunks[size_t(L.chunk)];
+        if (read_from_host(ch)) is.chunk_read(L, ch.copies[0], copy);
+      }
+    }
+    // the host was busy with these: the first level gets a start mark of its own
+    if (level_done < 0 && next_read + next_chunk > before) is.other(late_comp);
+  };
   auto issue_outbound = [&](size_t upto) {  // read out the first `upto` pieces
     while (issued < upto) {
-      // one launch per run of positions with the same alignment
+      // one launch per run of positions with the same alignment, up to the
+      // next position that host reads wait for
+      size_t stop = upto;
+      if (reads && next_read < c.host_reads.size() && size_t(c.host_reads[next_read].outs) > issued)
+        stop = std::min(stop, size_t(c.host_reads[next_read].outs));
       Launch L;
       L.kind = 3;
       L.aligned = c.out_aligned[issued] != 0;
       L.d0 = c.out_d0 + int(issued);
-      for (; issued < upto && (c.out_aligned[issued] != 0) == L.aligned; ++issued) {
+      for (; issued < stop && (c.out_aligned[issued] != 0) == L.aligned; ++issued) {
         L.tiles_max += c.out_tiles[issued];
         L.bytes += c.outbound[size_t(c.out_order[issued])].bytes;
       }
@@ -898,39 +977,10 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
       if (!cs.d2h0) cs.d2h0 = r.e0;
       cs.d2h1 = r.e1;
       cs.d2h_bytes += L.bytes;
+      issue_reads();
     }
   };
-  cs.d2h0 = cs.d2h1 = nullptr;
-
-  // ---- repack levels ---------------------------------------------------------------
-  hipEvent_t level0_end = nullptr;  // the KV outbound gathered at level 0 is copied out after it
-  cs.rep0 = nullptr;
-  // In place, the host reads run beside the levels, each launch once the
-  // levels up to its gate are done: the weights' on the side stream (with
-  // outbound reads they follow those instead), the KV chunks' on the copy
-  // stream, which nothing else of the call needs then.
-  size_t next_read = 0, next_chunk = 0;
-  auto due = [](const std::vector<Launch> &v, size_t i, int level) { return i < v.size() && v[i].gate <= level; };
-  auto read_up_to = [&](int level) {
-    const size_t before = next_read + next_chunk;
-    if (gated_reads && due(c.host_reads, next_read, level)) {
-      HIPCHK(hipStreamWaitEvent(E.side, is.mark_or_record(compute, true), 0));
-      is.other(E.side);
-      for (; due(c.host_reads, next_read, level); ++next_read) is.host_read(c.host_reads[next_read], E.side);
-    }
-    if (ring_pinned && due(c.chunk_reads, next_chunk, level)) {
-      HIPCHK(hipStreamWaitEvent(copy, is.mark_or_record(compute, true), 0));
-      is.other(copy);
-      for (; due(c.chunk_reads, next_chunk, level); ++next_chunk) {
-        const Launch &L = c.chunk_reads[next_chunk];
-        const Chunk &ch = c.chunks[size_t(L.chunk)];
-        if (read_from_host(ch)) is.chunk_read(L, ch.copies[0], copy);
-      }
-    }
-    // the host was busy with these: the first level gets a start mark of its own
-    if (level < 0 && next_read + next_chunk > before) is.other(compute);
-  };
-  read_up_to(-1);
+  issue_reads();
   for (size_t i = 0; i < c.levels.size(); ++i) {
     const Launch &L = c.levels[i];
     if (split) {
@@ -944,23 +994,27 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
     if (!cs.rep0) cs.rep0 = r.e0;
     cs.repack_bytes += 2 * L.bytes;
     if (L.level == 0) level0_end = r.e1;
-    if (i + 1 == c.levels.size() || c.levels[i + 1].level != L.level) read_up_to(L.level);
+    if (i + 1 == c.levels.size() || c.levels[i + 1].level != L.level) {
+      level_done = L.level;
+      issue_reads();
+    }
   }
-  read_up_to(c.n_levels);
-  if (gated_reads) is.end_host_reads(E.side);
-  if (ring_pinned) is.end_host_reads(copy);
+  level_done = c.n_levels;
   if (split) issue_outbound(c.out_order.size());  // pieces no level waits for
+  issue_reads();
+  if (reads) is.end_host_reads(reads);
+  if (ring_pinned) is.end_host_reads(copy);
   if (!cs.rep0) cs.rep0 = is.mark_or_record(late_comp, true);
   cs.rep1 = is.mark_or_record(late_comp, true);  // also: prepare and every level are done
 
-  // in place with outbound reads (or with the inflow buffer still being
-  // filled): the copy kernel reads every gated or strided inflow piece from
-  // the pinned host buffer into its final place after the last level and
-  // every outbound read
+  // in place with no stream for them above (or with the inflow buffer still
+  // being filled): the copy kernel reads every gated or strided inflow piece
+  // from the pinned host buffer into its final place after the last level
+  // and every outbound read
   const hipStream_t await_stream = P.inplace ? late_comp : E.side;
   if (await && !defer) {
     is.awaited(await_stream, *await);
-  } else if (!await && P.inplace && !gated_reads && !c.host_reads.empty()) {
+  } else if (inplace_reads && !reads) {
     for (const Launch &L : c.host_reads) is.host_read(L, late_comp);
     is.end_host_reads(late_comp);
   }
@@ -1009,12 +1063,13 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
   // ---- tails ----------------------------------------------------------------------
   // the last mark of each stream the call used; the inflow ends with the
   // later of h2d1 and hr1
-  auto tails = [&E, &cs, compute, copy, use_copy, side = use_side ? E.side : hipStream_t(nullptr)](Issuer &is) {
+  auto tails = [&cs, compute, copy, use_copy, reads, side = use_side ? E.side : hipStream_t(nullptr)](Issuer &is) {
     cs.tail_copy = cs.h2d1 = use_copy ? is.mark_or_record(copy, true) : nullptr;
     cs.tail_compute = is.mark_or_record(compute, false);
     // the side stream is not joined back into the caller's streams (that
     // would hold up the other call's work); atp_sync waits for it
     cs.tail_side = side ? is.mark_or_record(side, false) : nullptr;
+    cs.tail_reads = reads ? is.mark_or_record(reads, false) : nullptr;
   };
   tails(is);
   if (defer) {
@@ -1061,7 +1116,7 @@ int exec_sync(Plan &P, atp_timing *out) {
         rc = ae ? ae->code : ATP_EINVAL;
         msg = e.what();
       }
-      for (hipStream_t s : {c->compute, c->copy, E.side})
+      for (hipStream_t s : {c->compute, c->copy, E.side, E.reads})
         if (s && hipStreamSynchronize(s) != hipSuccess) (void)hipGetLastError();
     }
   }
@@ -1071,7 +1126,7 @@ int exec_sync(Plan &P, atp_timing *out) {
   for (int which = 0; which < 2; ++which) {
     CallState &cs = which == 0 ? E.w : E.k;
     if (!cs.pending) continue;
-    for (hipEvent_t e : {cs.tail_compute, cs.tail_copy, cs.tail_side}) {
+    for (hipEvent_t e : {cs.tail_compute, cs.tail_copy, cs.tail_side, cs.tail_reads}) {
       if (!e) continue;
       hipError_t err = hipEventSynchronize(e);
       if (err != hipSuccess) (void)hipGetLastError();  // reported below, as for hip_check
@@ -1158,7 +1213,7 @@ void exec_free(Plan &P) {
     // drain anything still queued before the pinned buffers go away
     for (CallState *c : {&E->w, &E->k}) {
       if (c->pending)
-        for (hipEvent_t e : {c->tail_compute, c->tail_copy, c->tail_side})
+        for (hipEvent_t e : {c->tail_compute, c->tail_copy, c->tail_side, c->tail_reads})
           if (e) (void)hipEventSynchronize(e);
       c->finish_issue = nullptr;  // a deferred issue never run: its readers stop and join
       release_scratch(*E, *c);
@@ -1187,6 +1242,7 @@ void exec_warmup(void *compute_, void *copy_, int events) {
   HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_spin)));
   HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_nop)));
   choose_side(E, compute, copy);
+  choose_reads(E);
   (void)scratch_of(E.device);  // the no-allocation entry point's scratch array, on this device
   for (int i = 0; i < events; ++i) {
     E.ev_sync();

@@ -1245,39 +1245,64 @@ void schedule(Plan &P, CallPlan &c, std::vector<Fam> &retained, std::vector<Pend
       ridx.query(d, [&](int a) { gate = std::max(gate, nodes[a].kind == Node::NORMAL ? nodes[a].level : 0); });
     return gate;
   };
-  // whether reads of `bytes` that wait for levels up to `gate` become a
-  // launch, or are merged with those of the next gate
-  auto reads_due = [&](uint64_t bytes, bool first, int gate) {
-    return bytes >= (first ? kReadFirst : kReadMin) || gate + 1 >= c.n_levels;
-  };
+  // whether reads of `bytes` become a launch, or are merged with the next ones
+  auto reads_due = [&](uint64_t bytes, bool first) { return bytes >= (first ? kReadFirst : kReadMin); };
   // host reads keep the narrow tile: more bytes in flight over PCIe would
   // slow the repack beside them
-  auto emit_reads = [&](const std::vector<Fam> &group, int gate) {
+  auto emit_reads = [&](const std::vector<Fam> &group, int gate, int outs) {
     const size_t before = c.host_reads.size();
     if (!group.empty()) emit_group(c, group, P.inplace ? c.n_levels : -1, 4, c.host_reads, live_hint, false);
-    for (size_t i = before; i < c.host_reads.size(); ++i) c.host_reads[i].gate = gate;
+    for (size_t i = before; i < c.host_reads.size(); ++i) {
+      c.host_reads[i].gate = gate;
+      c.host_reads[i].outs = outs;
+    }
   };
-  if (!P.inplace || !outbound.empty()) {
-    emit_reads(host_pieces, P.inplace ? c.n_levels - 1 : -1);
+  if (!P.inplace) {
+    emit_reads(host_pieces, -1, 0);
   } else {
-    // In place a piece may land once the last level that reads its
-    // destination is done, beside the levels that follow: the link is busy
-    // from the first of them on.  Gates are merged until a launch has
+    // In place a piece may land once the last level and the last outbound
+    // read that read its destination are done, beside those that follow: the
+    // link is busy, in both directions, from the first of them on.  Pieces
+    // are taken in the order they get ready in, merged until a launch has
     // kReadMin bytes (0.22 ms of the link, against a gap of 6 us between two
-    // launches).  Of the 8-layer TP 8->7 last-rank share (74.7 MB
-    // over the link, 12 levels of 0.38 ms) the step took 1.75 ms with every
-    // read after the last level and 1.48 ms with gates.
-    std::vector<std::vector<Fam>> by_gate(size_t(c.n_levels) + 1);
-    for (const Fam &f : host_pieces) by_gate[size_t(read_gate(dst_span(f, f.o_begin, f.o_end)) + 1)].push_back(f);
+    // launches).  With every read after the last level and outbound read, the
+    // 8-layer TP 8->7 last-rank share (74.7 MB in, 12 levels of 0.38 ms, no
+    // outbound) took 1.75 ms a step, with gates 1.48; the weights of the
+    // 4-layer 80-layer-shape TP 8->7 share (721 MB in, 587 MB out) 23.4 and 17.9.
+    //
+    // The side stream's order: before level l the outbound pieces it waits
+    // for, at the end the rest.
+    std::vector<int> before(size_t(c.n_levels), 0);  // outbound pieces issued before level l
+    for (size_t o = 0; o < outbound.size(); ++o)
+      if (needed_by[o] < c.n_levels) before[size_t(needed_by[o])] = std::max(before[size_t(needed_by[o])], pos[o] + 1);
+    for (int l = 1; l < c.n_levels; ++l) before[size_t(l)] = std::max(before[size_t(l)], before[size_t(l) - 1]);
+    struct Ready {
+      int at, gate, outs;
+      const Fam *f;
+    };
+    std::vector<Ready> order;
+    for (const Fam &f : host_pieces) {
+      const Span d = dst_span(f, f.o_begin, f.o_end);
+      Ready r{0, read_gate(d), out_gate(d), &f};
+      if (r.gate >= 0) r.at = before[size_t(r.gate)] + r.gate + 1;
+      if (r.outs > 0) {
+        int l = 0;
+        while (l < c.n_levels && before[size_t(l)] < r.outs) ++l;
+        r.at = std::max(r.at, r.outs + l);
+      }
+      order.push_back(r);
+    }
+    std::stable_sort(order.begin(), order.end(), [](const Ready &x, const Ready &y) { return x.at < y.at; });
     std::vector<Fam> group;
     uint64_t bytes = 0;
-    for (int gate = -1; gate < c.n_levels; ++gate) {
-      for (const Fam &f : by_gate[size_t(gate + 1)]) {
-        group.push_back(f);
-        bytes += f.bytes();
-      }
-      if (!reads_due(bytes, c.host_reads.empty(), gate)) continue;
-      emit_reads(group, gate);
+    int gate = -1, outs = 0;
+    for (size_t i = 0; i < order.size(); ++i) {
+      group.push_back(*order[i].f);
+      bytes += order[i].f->bytes();
+      gate = std::max(gate, order[i].gate);
+      outs = std::max(outs, order[i].outs);
+      if (i + 1 < order.size() && (order[i + 1].at == order[i].at || !reads_due(bytes, c.host_reads.empty()))) continue;
+      emit_reads(group, gate, outs);
       group.clear();
       bytes = 0;
     }
@@ -1387,7 +1412,7 @@ void schedule(Plan &P, CallPlan &c, std::vector<Fam> &retained, std::vector<Pend
         group.push_back(u);
         bytes += c.fams[size_t(u.d)].bytes();
       }
-      if (!reads_due(bytes, c.chunk_reads.empty(), gate)) continue;
+      if (!reads_due(bytes, c.chunk_reads.empty()) && gate + 1 < c.n_levels) continue;
       std::sort(group.begin(), group.end(), [](const Unit &x, const Unit &y) { return x.d < y.d; });
       for (const Unit &u : group) {
         const bool joins = !c.chunk_reads.empty() && c.chunk_reads.back().gate == gate &&

@@ -65,6 +65,7 @@ struct Launch {
   uint64_t tiles_max = 0;
   std::vector<int> wait_outbound;  // outbound copies that must finish first
   int gate = -1;  // host read: the level that must be done first (-1: none)
+  int outs = 0;   // host read: the outbound reads, in issue order, that must be done first
   int chunk = -1; // host read of a landing-ring chunk
 };
 
@@ -103,9 +104,8 @@ struct CallPlan {
   std::vector<int> out_order;   // outbound issue order (by the level needing it)
   // Inflow other than large contiguous gaps is read by the copy kernel
   // straight from the pinned inflow buffer (host_reads): out of place from
-  // the call's start; in place beside the levels, each launch after the
-  // level it is gated on, or after the last level where outbound reads gate
-  // it too.  In place, no
+  // the call's start; in place beside the levels and the outbound reads,
+  // each launch after those it is gated on.  In place, no
   // host-to-device copy command waits long for an event: such a command
   // holds up every later host-to-device copy of the process on the DMA
   // engine (the in-place KV inflow takes the landing ring, which waits only
