@@ -336,6 +336,19 @@ bool kernel_readable(const void *p, uint64_t bytes) {
   return true;
 }
 
+// One allocation holds all of the buffer: memory that is pinned at both ends
+// may still be pageable between them.
+bool one_allocation(const void *p, uint64_t bytes) {
+  hipDeviceptr_t base{};
+  size_t size = 0;
+  if (hipMemGetAddressRange(&base, &size, const_cast<void *>(p)) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  const uintptr_t b = reinterpret_cast<uintptr_t>(base), a = reinterpret_cast<uintptr_t>(p);
+  return a >= b && a - b <= size && bytes <= size - (a - b);
+}
+
 void check_kernel_host_buffer(const void *p, uint64_t bytes, const char *what) {
   if (!bytes) return;
   if (!p) throw Error(ATP_EINVAL, std::string(what) + " is NULL");
@@ -754,7 +767,8 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
   // at 30 in others, for all of a process's passes after the first, so that
   // the 4-layer TP 8->7 reshard in place took 52.1 ms a step or 81.9; read
   // by the kernel it takes 51.4 (80 layers: 1017 -> 1008).
-  const bool ring_pinned = !c.chunks.empty() && kernel_readable(inflow_host, inflow_bytes);
+  const bool ring_pinned = !c.chunks.empty() && kernel_readable(inflow_host, inflow_bytes) &&
+                           one_allocation(inflow_host, inflow_bytes);
   auto read_from_host = [ring_pinned](const Chunk &ch) {
     return ring_pinned && ch.copies.size() == 1 && ch.copies[0].host_off % 16 == ch.copies[0].dev_off % 16;
   };

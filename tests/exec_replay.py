@@ -59,6 +59,8 @@ def run(case):
         aw, nw, ak, nk = dmalloc(aw_n), dmalloc(st.new_arena_bytes), dmalloc(ak_n), dmalloc(st.new_kv_bytes)
     sw, sk, td = dmalloc(st.staging_w), dmalloc(st.staging_kv), dmalloc(table.nbytes)
     hin_w, hin_k = hmalloc(st.inflow_w), hmalloc(st.inflow_kv)
+    if case.get("split_kv_inflow"):
+        mock.mock_split_host(C.c_void_p(hin_k))
     hout_w, hout_k = hmalloc(st.outbound_w), hmalloc(st.outbound_kv)
     s0, s1 = stream(), stream()
     if case["warmup"]:

@@ -26,6 +26,7 @@ std::map<uintptr_t, Alloc> allocs;  // by base
 uintptr_t next_dev = uintptr_t(1) << 44, next_fake_host = uintptr_t(3) << 44;
 std::set<void *> events, streams;
 std::set<void *> recorded;
+std::set<uintptr_t> split;  // host allocations of which only the first and last page count as pinned
 long launches = 0, copies = 0, waits = 0;
 dim3 cfg_grid, cfg_block;
 size_t cfg_shmem;
@@ -116,12 +117,22 @@ hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *p) {
   std::lock_guard<std::mutex> g(mu);
   const Alloc *x = find(p, 1);
   memset(a, 0, sizeof(*a));
+  if (x && split.count(x->b) && uintptr_t(p) >= x->b + 4096 && uintptr_t(p) < x->e - 4096) x = nullptr;
   if (!x) { last = hipErrorInvalidValue; return hipErrorInvalidValue; }
   a->type = x->host ? hipMemoryTypeHost : hipMemoryTypeDevice;
   a->hostPointer = x->host ? (void *)p : nullptr;
   a->devicePointer = (void *)p;
   return hipSuccess;
 }
+hipError_t hipMemGetAddressRange(hipDeviceptr_t *base, size_t *n, hipDeviceptr_t p) {
+  std::lock_guard<std::mutex> g(mu);
+  const Alloc *x = find(p, 1);
+  if (!x) { last = hipErrorNotFound; return hipErrorNotFound; }
+  *base = (hipDeviceptr_t)x->b;
+  *n = split.count(x->b) ? 4096 : x->e - x->b;
+  return hipSuccess;
+}
+void mock_split_host(void *p) { std::lock_guard<std::mutex> g(mu); split.insert(uintptr_t(p)); }
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind k, hipStream_t st) {
   std::lock_guard<std::mutex> g(mu);
   if (st && !streams.count(st)) die("copy on an unknown stream", st, 0);

@@ -64,6 +64,17 @@ def test_in_place_weights_first_and_kv_first_refused(mockhip):
     assert res[3]["refused"] == -5 and "before" in res[3]["msg"]
 
 
+def test_in_place_kv_inflow_pinned_at_both_ends_only(mockhip):
+    """An in-place KV inflow buffer whose first and last page are pinned apart,
+    with pageable memory between, takes the landing ring's copies: the copy
+    kernel would fault on it."""
+    case = {"w": 5, "inplace": True, "order": "weights-first", "steps": 1, "warmup": False}
+    whole, = _replay(mockhip, [case])
+    split, = _replay(mockhip, [dict(case, split_kv_inflow=True)])
+    assert whole["ok"] and split["ok"]
+    assert split["mock_copies"] > whole["mock_copies"]
+
+
 def test_async_load_with_the_kv_call_between(mockhip, tmp_path):
     """atp_load_reshard_weights_async, the KV call while the reads run, then
     atp_sync issuing the weight pieces: in and out of place, fresh plans in
