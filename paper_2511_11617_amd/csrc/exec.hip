@@ -833,7 +833,13 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
 
   const double t_repack = 2 * double(P.w.moved + P.k.moved) / kRepackRate,
                t_reads = double(P.w.inflow + P.k.inflow) / kLinkRate;
-  const LinkGrid &read_grid = do_out && !kvcall && !await       ? kHostReadBesideOutbound
+  // In place: where the KV inflow outlasts the outbound reads, the link is
+  // busy inwards beside them without the weight inflow, and twice the reads
+  // in flight slow the outbound reads and the levels: with the weight inflow
+  // beside them too the 80-layer TP 8->7 share took 1035 ms and 17.0 ms of
+  // repack a step, with it after them 1021 and 16.1 (4 layers: 51.0, 51.2).
+  const bool kv_covers = double(P.k.inflow) * kOutboundRate >= double(c.outbound_bytes) * kLinkRate;
+  const LinkGrid &read_grid = do_out && !kvcall && !await && !kv_covers ? kHostReadBesideOutbound
                               : t_repack >= 0.25 * t_reads ? kHostReadBesideRepack
                                                            : kHostRead;
   Issuer is{E, cs, c, kvcall ? P.kv.num_blocks : 0, kvcall ? P.kv.live_blocks : 0, b_out, b_st, host_in, read_grid,
@@ -851,10 +857,11 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
   const bool inplace_reads = P.inplace && !c.host_reads.empty() && !await;
   const bool use_side = do_out || early_reads || inplace_reads;
   if (use_side) choose_side(E, compute, copy);
-  if (inplace_reads && do_out) choose_reads(E);
+  const bool own_queue = inplace_reads && do_out && !kv_covers;
+  if (own_queue) choose_reads(E);
   // in place, the stream that reads beside the levels: null where only a
   // queue of its own would do and none is free
-  const hipStream_t reads = inplace_reads ? (do_out ? E.reads : E.side) : nullptr;
+  const hipStream_t reads = inplace_reads ? (own_queue ? E.reads : do_out ? nullptr : E.side) : nullptr;
 
   // every stream of this call starts after what the caller has queued on
   // `compute` when the call is made (with the other call of the plan
@@ -923,8 +930,7 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
   // That work and the weight inflow read after it stay off the caller's
   // streams, so that they do not hold up the other call's work queued
   // behind them.
-  const LinkGrid &out_grid = double(P.k.inflow) * kOutboundRate >= double(c.outbound_bytes) * kLinkRate
-                                 ? kOutboundBesideReads : kOutbound;
+  const LinkGrid &out_grid = kv_covers ? kOutboundBesideReads : kOutbound;
   size_t issued = 0;  // outbound pieces read out so far, in plan order
   const bool split = do_out && !kvcall;
   hipStream_t late_comp = compute;
@@ -1029,7 +1035,19 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
   if (await && !defer) {
     is.awaited(await_stream, *await);
   } else if (inplace_reads && !reads) {
-    for (const Launch &L : c.host_reads) is.host_read(L, late_comp);
+    // nothing to wait for in between: neighbouring launches go as one (12 MiB
+    // each, they took 3 ms more for the 80 layers' 13.3 GB)
+    for (size_t i = 0; i < c.host_reads.size();) {
+      Launch L = c.host_reads[i];
+      for (++i; i < c.host_reads.size(); ++i) {
+        const Launch &n = c.host_reads[i];
+        if (n.d0 != L.d1 || n.aligned != L.aligned || n.wide != L.wide) break;
+        L.d1 = n.d1;
+        L.bytes += n.bytes;
+        L.tiles_max += n.tiles_max;
+      }
+      is.host_read(L, late_comp);
+    }
     is.end_host_reads(late_comp);
   }
 

@@ -1199,12 +1199,13 @@ void schedule(Plan &P, CallPlan &c, std::vector<Fam> &retained, std::vector<Pend
     // command and each event between them costing it tens of microseconds.
     // Every other piece is read by the copy kernel straight from the pinned
     // host buffer into its final place: out of place from the start, beside
-    // the repack (the two write disjoint bytes); in place, for the weights,
-    // after the last level, since a copy command that waits for a level or
-    // an outbound read holds up every later host-to-device copy on the DMA
-    // engine.  The in-place KV landings go through the landing ring, whose
-    // copies wait only for their slot's previous scatter and land while the
-    // KV levels run.
+    // the repack (the two write disjoint bytes); in place beside the levels
+    // and outbound reads that no longer read its destination, since a copy
+    // command that waits for a level or an outbound read holds up every later
+    // host-to-device copy on the DMA engine.  The in-place KV landings are
+    // planned through the landing ring, whose copies wait only for their
+    // slot's previous scatter; from a pinned buffer the copy kernel reads
+    // them beside the KV levels instead.
     if (pd.contiguous && pd.fam.bytes() >= kDirectMin) {
       HostCopy h;
       h.host_off = pd.host_off;

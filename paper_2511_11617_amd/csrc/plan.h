@@ -108,9 +108,9 @@ struct CallPlan {
   // each launch after those it is gated on.  In place, no
   // host-to-device copy command waits long for an event: such a command
   // holds up every later host-to-device copy of the process on the DMA
-  // engine (the in-place KV inflow takes the landing ring, which waits only
-  // for its own scatters).  The weights' outbound
-  // reads are copy-kernel descriptors too (out_d0 + k for position k of
+  // engine (an in-place KV inflow that chunk_reads cannot read takes the
+  // landing ring, which waits only for its own scatters).  The weights'
+  // outbound reads are copy-kernel descriptors too (out_d0 + k for position k of
   // out_order), writing straight into the pinned outbound buffer: the
   // runtime's own device-to-host copies are wide blit kernels that starve
   // the HBM-bound repack beside them.
