@@ -837,7 +837,7 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
   // busy inwards beside them without the weight inflow, and twice the reads
   // in flight slow the outbound reads and the levels: with the weight inflow
   // beside them too the 80-layer TP 8->7 share took 1035 ms and 17.0 ms of
-  // repack a step, with it after them 1021 and 16.1 (4 layers: 51.0, 51.2).
+  // repack a step, with it after them 1016 and 16.0 (4 layers: 51.0, 51.1).
   const bool kv_covers = double(P.k.inflow) * kOutboundRate >= double(c.outbound_bytes) * kLinkRate;
   const LinkGrid &read_grid = do_out && !kvcall && !await && !kv_covers ? kHostReadBesideOutbound
                               : t_repack >= 0.25 * t_reads ? kHostReadBesideRepack
