@@ -431,7 +431,9 @@ void check_extents(const CallPlan &c, bool kvcall, const Plan &P, uint64_t in_by
       if (e > lim) throw Error(ATP_ECAPACITY, "a copy would run past the end of a buffer");
     }
     uint64_t lines = uint64_t(kvcall ? std::max<int64_t>(nb, f.o_end - f.o_begin) : f.o_end - f.o_begin) * f.rows;
-    if (lines * (f.run / 16 + 1) >= (uint64_t(1) << 32)) throw Error(ATP_EINVAL, "copy family too large");
+    // (the descriptors' run is 32 bits wide)
+    if (f.run > UINT32_MAX || lines * (f.run / 16 + 1) >= (uint64_t(1) << 32))
+      throw Error(ATP_EINVAL, "copy family too large");
   }
   // a launch's kernel tiles its descriptors the way the prepare kernel
   // counted them: the flags of every descriptor must match the launch

@@ -383,11 +383,11 @@ __device__ __forceinline__ void tile_addr(const Desc &x, uint64_t cbase, uint64_
       }
       col = uint32_t(c - C(line) * x.cpl);
     }
-    int32_t off = int32_t(col * 16);
+    uint64_t off = uint64_t(col) * 16;  // a line may be just under 4 GiB long
     if (ANY) {
       const uint32_t h = uint32_t(uintptr_t((x.flags & DF_SRC_GRID) ? la.src : la.dst)) & 15;
-      const int32_t o = off - int32_t(h), omax = int32_t(x.run) - 16;
-      off = o < 0 ? 0 : (o > omax ? omax : o);
+      const uint64_t omax = uint64_t(x.run) - 16;
+      off = off < h ? 0 : (off - h > omax ? omax : off - h);
     }
     sp[k] = la.src + off;
     dp[k] = la.dst + off;
