@@ -481,6 +481,14 @@ constexpr LinkGrid kHostRead = {32, 10, 32, false};
 // one tile was 0.8 % ahead.
 constexpr LinkGrid kHostReadBesideRepack = {20, 10, 32, true};
 constexpr double kRepackRate = 6000;
+// In-place KV lines whose items are not whole KiBs: a wavefront's chunks then
+// lie in several items and wait for a block id per lane, and with 10
+// workgroups of wide tiles the link idled meanwhile.  us for a KV call of 417
+// MB in 1280 B lines / 516 MB in 2560 B lines: wide tiles on 10 / 14 / 32
+// workgroups 10650 / 7800 / 7530 and 10200 / 9270 / 9480; narrow tiles, two in
+// flight, on 20 / 24 / 28 / 32 workgroups 7880 / 7550 / 7530 / 7535 and 9450 /
+// 9180 / 9240 / 9440; through the landing ring 7550 and 9275.
+constexpr LinkGrid kHostReadAcross = {24, 10, 32, true};
 // The outbound reads get a narrow grid: wide device-to-host writers (the
 // runtime's 512-workgroup blits) slowed a concurrent HBM-bound repack
 // several-fold; 64 KiB in flight leave a concurrent HBM copy at full speed
@@ -597,9 +605,12 @@ struct Issuer {
   // the slot, so the base moves until the slot's bytes are the chunk's bytes
   // of the inflow buffer
   void chunk_read(const Launch &L, const HostCopy &h, hipStream_t s) {
+    bool across = false;
+    for (int d = L.d0; d < L.d1; ++d) across = across || !whole_waves(c.fams[size_t(d)]);
+    const LinkGrid &grid = across ? kHostReadAcross : read_grid;
     char *base = reinterpret_cast<char *>(reinterpret_cast<uintptr_t>(host_in) + h.host_off - h.dev_off);
     timed(4, -1, L.bytes, s, [&] {
-      launch_copy(L, dev_desc, dev_prefix, nullptr, b_out, base, dev_live, s, &read_grid);
+      launch_copy(L, dev_desc, dev_prefix, nullptr, b_out, base, dev_live, s, &grid);
     });
     cs.h2d_bytes += L.bytes;
   }

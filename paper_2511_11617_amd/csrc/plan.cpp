@@ -758,7 +758,8 @@ uint64_t fam_tiles(const Fam &f, int64_t items_hint) {
 constexpr uint64_t kJoinMax = 8ull << 20;
 
 // Emit launches for a group of families: aligned ones first (with wide
-// tiles, if `allow_wide`, for short KV lines), then the ones that are not.
+// tiles, if `allow_wide`, for short KV lines; a landing-ring chunk's only where
+// they make whole waves, see kHostReadAcross), then the ones that are not.
 // Families are appended to c.fams; every family of a launch has the same
 // DF_ALIGNED and DF_WIDE flags.
 void emit_group(CallPlan &c, std::vector<Fam> group, int level, int kind, std::vector<Launch> &out,
@@ -772,7 +773,8 @@ void emit_group(CallPlan &c, std::vector<Fam> group, int level, int kind, std::v
       continue;
     }
     f.flags |= DF_ALIGNED;
-    if (allow_wide && f.run <= kWideMaxRun && (f.flags & (DF_SRC_IND | DF_DST_IND | DF_BLOCKRANGE)))
+    if (allow_wide && f.run <= kWideMaxRun && (f.flags & (DF_SRC_IND | DF_DST_IND | DF_BLOCKRANGE)) &&
+        (kind != 2 || whole_waves(f)))
       f.flags |= DF_WIDE;
     else
       narrow += uint64_t(std::min<int64_t>(f.o_end - f.o_begin, live_hint)) * f.rows * f.run;

@@ -40,6 +40,10 @@ struct Fam {
   uint64_t bytes() const { return uint64_t(o_end - o_begin) * rows * run; }
 };
 
+// A wavefront's 64 chunks lie in one outer item of a packed side: its block
+// id then comes through one scalar load.
+inline bool whole_waves(const Fam &f) { return f.rows * f.run % (64 * 16) == 0; }
+
 struct SpacePlan {
   int64_t H = 0;
   int N = 0, M = 0;

@@ -4,9 +4,11 @@ prints one line per case.  No torch, no GPU.
 
 argv: a JSON list of cases {"w": workload, "inplace": bool, "order":
 "weights-first" | "kv-first" | "async-load", "steps": n, "warmup": bool,
-"layers": optional layer count}.  "async-load" reads the weight inflow
-from a checkpoint of holes (atp_load_reshard_weights_async), issues the KV
-call while the reads run and lets atp_sync issue the weight pieces.
+"layers": optional layer count, "shape": optional changes of the workload's
+shape, "log": whether to return the last step's launches and copies}.
+"async-load" reads the weight inflow from a checkpoint of holes
+(atp_load_reshard_weights_async), issues the KV call while the reads run and
+lets atp_sync issue the weight pieces.
 """
 import ctypes as C
 import json
@@ -45,6 +47,7 @@ def run(case):
     c = configs.get(case["w"], inplace=case["inplace"])
     if case.get("layers"):
         c["layers"] = case["layers"]
+    c.update(case.get("shape", {}))
     table, pool = pagetable.make_for(c)
     n_live = len(np.unique(table[table >= 0]))
     inplace = bool(c["inplace"])
@@ -74,6 +77,7 @@ def run(case):
         names = [checkpoint.name(n, l) for (n, l, *_) in tl]
     launches = []
     for _ in range(case["steps"]):
+        mock.mock_log_clear()
         p = b.plan()
 
         def wcall():
@@ -104,7 +108,13 @@ def run(case):
         if case["order"] == "async-load":
             assert p.load_stats().bytes == st.inflow_w
         launches.append(int(t.n_launches))
-    return {"ok": True, "launches": launches, "mock_launches": int(mock.mock_launches()),
+    log = {}
+    if case.get("log"):
+        mock.mock_log.restype = C.c_char_p
+        roles = {s0: "compute", s1: "copy"}
+        log = {"log": [(n, int(k), roles.get(int(s), "side")) for n, k, s in
+                       (x.split() for x in mock.mock_log().decode().splitlines())]}
+    return {"ok": True, **log, "launches": launches, "mock_launches": int(mock.mock_launches()),
             "mock_copies": int(mock.mock_copies()), "streams": int(mock.mock_streams())}
 
 

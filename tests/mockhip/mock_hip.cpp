@@ -10,6 +10,8 @@
 //     launches need a non-empty grid.  A violation prints MOCKHIP FAULT and
 //     aborts the process.
 //   * Kernels are counted, not run; events time 0.125 ms.
+//   * mock_log() lists the launches ("kernel name, workgroups, stream") and
+//     copies ("copy, bytes, stream") since mock_log_clear(), one a line.
 #include <hip/hip_runtime_api.h>
 #include <cstdio>
 #include <cstdlib>
@@ -17,6 +19,7 @@
 #include <map>
 #include <mutex>
 #include <set>
+#include <string>
 #include <vector>
 
 namespace {
@@ -27,6 +30,8 @@ uintptr_t next_dev = uintptr_t(1) << 44, next_fake_host = uintptr_t(3) << 44;
 std::set<void *> events, streams;
 std::set<void *> recorded;
 std::set<uintptr_t> split;  // host allocations of which only the first and last page count as pinned
+std::map<const void *, std::string> names;  // kernels by host function
+std::string log_text;
 long launches = 0, copies = 0, waits = 0;
 dim3 cfg_grid, cfg_block;
 size_t cfg_shmem;
@@ -143,13 +148,15 @@ hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind k, hip
   if (k == hipMemcpyDeviceToHost && (xs->host || !xd->host)) die("D2H copy with wrong sides", d, n);
   if (xd->host && xd->real && xs->host && xs->real) memcpy(d, s, n);
   ++copies;
+  log_text += "copy " + std::to_string(n) + " " + std::to_string(uintptr_t(st)) + "\n";
   return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void *, dim3 g, dim3 b, void **, size_t, hipStream_t s) {
+hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **, size_t, hipStream_t s) {
   std::lock_guard<std::mutex> lk(mu);
   if (s && !streams.count(s)) die("launch on an unknown stream", s, 0);
   if (g.x == 0 || b.x == 0) die("empty launch", nullptr, 0);
   ++launches;
+  log_text += names[f] + " " + std::to_string(g.x) + " " + std::to_string(uintptr_t(s)) + "\n";
   return hipSuccess;
 }
 hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t sh, hipStream_t s) {
@@ -159,7 +166,7 @@ hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *sh, hipStream_t *
   *g = cfg_grid; *b = cfg_block; *sh = cfg_shmem; *s = cfg_stream; return hipSuccess;
 }
 void **__hipRegisterFatBinary(const void *) { static void *h[1]; return h; }
-void __hipRegisterFunction(void **, const void *, char *, const char *, unsigned int, void *, void *, void *, void *, int *) {}
+void __hipRegisterFunction(void **, const void *f, char *, const char *name, unsigned int, void *, void *, void *, void *, int *) { names[f] = name; }
 void __hipRegisterVar(void **, void *, char *, const char *, int, size_t, int, int) {}
 void __hipUnregisterFatBinary(void **) {}
 hipError_t hipFuncGetAttributes(hipFuncAttributes *a, const void *) { memset(a, 0, sizeof(*a)); return hipSuccess; }
@@ -175,6 +182,8 @@ hipError_t hipIpcGetMemHandle(hipIpcMemHandle_t *, void *) { return hipErrorNotS
 hipError_t hipIpcOpenMemHandle(void **, hipIpcMemHandle_t, unsigned) { return hipErrorNotSupported; }
 hipError_t hipIpcCloseMemHandle(void *) { return hipErrorNotSupported; }
 // statistics for the driver
+const char *mock_log(void) { return log_text.c_str(); }
+void mock_log_clear(void) { log_text.clear(); }
 long mock_launches(void) { return launches; }
 long mock_copies(void) { return copies; }
 long mock_waits(void) { return waits; }

@@ -75,6 +75,21 @@ def test_in_place_kv_inflow_pinned_at_both_ends_only(mockhip):
     assert split["mock_copies"] > whole["mock_copies"]
 
 
+@pytest.mark.parametrize("layout,head_dim,kernel,groups", [
+    ("head", 128, "k_copy_linkILi4E", 10),   # items of 4096 bytes
+    ("head", 80, "k_copy_linkILi2E", 24),    # 2560: waves cross items
+    ("token", 128, "k_copy_linkILi4E", 10),  # 16 tokens of 256 bytes
+    ("token", 72, "k_copy_linkILi2E", 24)])  # 16 of 144
+def test_in_place_kv_reads_of_lines_that_cross_waves(mockhip, layout, head_dim, kernel, groups):
+    """In-place KV lines whose items are not whole KiBs are read with narrow
+    tiles on 24 workgroups: wide ones on 10 left the link idle."""
+    case = {"w": 5, "inplace": True, "order": "weights-first", "steps": 1, "warmup": False, "layers": 2, "log": True,
+            "shape": {"kv_layout": layout, "head_dim": head_dim, "n_seq": 16, "seq_tokens": 1024}}
+    r, = _replay(mockhip, [case])
+    reads = [(n, g) for n, g, stream in r["log"] if stream == "copy" and "k_copy" in n]
+    assert reads and all(kernel in n and g == groups for n, g in reads), reads
+
+
 def test_async_load_with_the_kv_call_between(mockhip, tmp_path):
     """atp_load_reshard_weights_async, the KV call while the reads run, then
     atp_sync issuing the weight pieces: in and out of place, fresh plans in
