@@ -368,8 +368,8 @@ int atp_plan_launches(const atp_plan_t *plan, atp_launch *out, int32_t cap, int3
  *   H2D_RING host inflow -> landing-ring slot (staging), then the SCATTER
  *            copies that follow it, after all levels; where a slot takes
  *            one H2D_RING copy and the inflow buffer is pinned, each
- *            SCATTER reads that buffer instead, once level `level` has
- *            finished (-1: at any time)
+ *            SCATTER may read that buffer instead, as early as level
+ *            `level` has finished (-1: at any time)
  *   H2D      host inflow -> arena, allowed once level `level` has
  *            finished (level -1: at any time) and the first `after_d2h`
  *            D2H copies of the list have finished

@@ -6,8 +6,8 @@
 // the host buffer, out of place beside the repack on a side stream that
 // feeds a hardware queue of its own, in place beside the levels that no
 // longer read its destination, or after the last one; the
-// in-place KV inflow chunk by chunk, or from pageable memory through the
-// landing ring plus a scatter kernel), reads
+// in-place KV inflow chunk by chunk, or through the landing ring plus a
+// scatter kernel: from pageable memory, or where it would wait too long), reads
 // dropped outbound bytes out before an in-place overwrite (the copy kernel
 // writing the host buffer, on the side stream), and orders all of it with
 // HIP events.
@@ -614,6 +614,18 @@ struct Issuer {
     });
     cs.h2d_bytes += L.bytes;
   }
+  // a landing-ring chunk into its slot, at once; returns its end mark
+  hipEvent_t slot_read(const HostCopy &h, hipStream_t s) {
+    const uint64_t n = h.bytes / 16, tiles = (n + kTileChunks - 1) / kTileChunks;
+    const CallState::LaunchRec r = timed(4, -1, h.bytes, s, [&] {
+      hipLaunchKernelGGL(k_copy_linear, dim3(unsigned(std::min<uint64_t>(tiles, kHostReadBesideRepack.narrow))),
+                         dim3(kThreads), 0, s, reinterpret_cast<const u32x4 *>(host_in + h.host_off),
+                         reinterpret_cast<u32x4 *>(b_st + h.dev_off), n);
+      HIPCHK(hipGetLastError());
+    });
+    cs.h2d_bytes += h.bytes;
+    return r.e1;
+  }
   void end_host_reads(hipStream_t s) { cs.hr1 = mark_or_record(s, true); }
   // While the inflow buffer is still being filled, the direct landings and
   // the host reads (each launch cut at descriptor boundaries into pieces of
@@ -782,8 +794,13 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
   // by the kernel it takes 51.4 (80 layers: 1017 -> 1008).
   const bool ring_pinned = !c.chunks.empty() && kernel_readable(inflow_host, inflow_bytes) &&
                            one_allocation(inflow_host, inflow_bytes);
-  auto read_from_host = [ring_pinned](const Chunk &ch) {
-    return ring_pinned && ch.copies.size() == 1 && ch.copies[0].host_off % 16 == ch.copies[0].dev_off % 16;
+  // The first ones may land in their slots all the same, read by the copy
+  // kernel at once (CallPlan::slot_chunks; on one stream they would hold up
+  // the levels).
+  const int slot_chunks = ring_pinned && copy != compute ? c.slot_chunks : 0;
+  auto read_from_host = [ring_pinned, slot_chunks, &c](const Chunk &ch) {
+    return ring_pinned && &ch - c.chunks.data() >= slot_chunks && ch.copies.size() == 1 &&
+           ch.copies[0].host_off % 16 == ch.copies[0].dev_off % 16;
   };
   if (!c.host_reads.empty()) check_kernel_host_buffer(inflow_host, inflow_bytes, "inflow buffer");
   if (do_out && c.out_d0 >= 0) check_kernel_host_buffer(outbound_host, c.outbound_bytes, "outbound buffer");
@@ -895,6 +912,12 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
   // so that the host does not wait for the reads before the repack is queued.
   if (!await)
     for (const HostCopy &h : c.directs) is.direct(h);
+
+  std::vector<hipEvent_t> slot_landed;
+  for (int i = 0; i < slot_chunks; ++i) {
+    if (i == 0) is.other(copy);
+    slot_landed.push_back(is.slot_read(c.chunks[size_t(i)].copies[0], copy));
+  }
 
   // ---- prepare: descriptors into staging, block list, tile counts ------------------
   PrepArgs pa{};
@@ -1084,17 +1107,23 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
   // through the ring: H2D into a slot (once the slot's previous scatter is
   // done), then a scatter from it after every level
   std::vector<hipEvent_t> slot_free(size_t(c.n_slots), nullptr);
-  for (const Chunk &ch : c.chunks) {
+  for (size_t i = 0; i < c.chunks.size(); ++i) {
+    const Chunk &ch = c.chunks[i];
     if (read_from_host(ch)) continue;
-    is.other(copy);
     hipEvent_t &free = slot_free[size_t(ch.slot)];
-    if (free) HIPCHK(hipStreamWaitEvent(copy, free, 0));
-    for (const HostCopy &h : ch.copies) {
-      HIPCHK(hipMemcpyAsync(b_st + h.dev_off, host_in + h.host_off, h.bytes, hipMemcpyHostToDevice, copy));
-      cs.h2d_bytes += h.bytes;
+    hipEvent_t landed = nullptr;
+    if (i < slot_landed.size()) {
+      landed = slot_landed[i];
+    } else {
+      is.other(copy);
+      if (free) HIPCHK(hipStreamWaitEvent(copy, free, 0));
+      for (const HostCopy &h : ch.copies) {
+        HIPCHK(hipMemcpyAsync(b_st + h.dev_off, host_in + h.host_off, h.bytes, hipMemcpyHostToDevice, copy));
+        cs.h2d_bytes += h.bytes;
+      }
+      landed = E.ev_sync();
+      HIPCHK(hipEventRecord(landed, copy));
     }
-    hipEvent_t landed = E.ev_sync();
-    HIPCHK(hipEventRecord(landed, copy));
     HIPCHK(hipStreamWaitEvent(late_comp, landed, 0));
     is.other(late_comp);
     for (const Launch &L : ch.scatters) {
@@ -1283,6 +1312,7 @@ void exec_warmup(void *compute_, void *copy_, int events) {
   HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy16<kUnroll>)));
   HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy16<kWideUnroll>)));
   HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy_any)));
+  HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy_linear)));
   HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_prepare)));
   HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_spin)));
   HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_nop)));

@@ -12,6 +12,7 @@
 //                 512 consecutive chunks (8 KiB) of one descriptor.
 //   k_copy_link   the same over the link to the host, on a narrow persistent
 //                 grid with two tiles in flight per workgroup.
+//   k_copy_linear contiguous bytes of the host buffer into a landing-ring slot.
 //   k_copy_any    the same for lines that are not 16-byte aligned (odd column
 //                 counts): unaligned 16-byte accesses on one side, the
 //                 chunks of a line cut at the other side's boundaries.
@@ -561,6 +562,49 @@ __global__ void __launch_bounds__(kThreads) k_copy_link(const Desc *__restrict__
     while (prefix[d + 1] <= t) ++d;
     x.load(descs[d], t - prefix[d], b0, b1, b2, live);
     y.store();
+  }
+}
+
+// Contiguous bytes of the pinned inflow buffer into a landing-ring slot, at
+// once: it needs no descriptor, so it does not wait for k_prepare.  Two tiles
+// of a workgroup in flight, as in k_copy_link, on a grid as narrow.
+struct LinearTile {
+  u32x4 v[kUnroll];
+  uint64_t at;
+
+  __device__ __forceinline__ void load(const u32x4 *src, uint64_t tile, uint64_t n) {
+    at = tile * kTileChunks + threadIdx.x;
+#pragma unroll
+    for (int k = 0; k < kUnroll; ++k) {
+      const uint64_t i = at + uint64_t(k) * kThreads;
+      v[k] = load16(src + (i < n ? i : n - 1));
+    }
+  }
+  // lanes past the end store the last chunk once more
+  __device__ __forceinline__ void store(u32x4 *dst, uint64_t n) const {
+#pragma unroll
+    for (int k = 0; k < kUnroll; ++k) {
+      const uint64_t i = at + uint64_t(k) * kThreads;
+      store16(dst + (i < n ? i : n - 1), v[k]);
+    }
+  }
+};
+
+__global__ void __launch_bounds__(kThreads) k_copy_linear(const u32x4 *src, u32x4 *dst, uint64_t n) {
+  const uint64_t T = (n + kTileChunks - 1) / kTileChunks;
+  uint64_t t = blockIdx.x;
+  if (t >= T) return;
+  LinearTile x, y;
+  x.load(src, t, n);
+  for (;;) {
+    t += gridDim.x;
+    if (t >= T) return x.store(dst, n);
+    y.load(src, t, n);
+    x.store(dst, n);
+    t += gridDim.x;
+    if (t >= T) return y.store(dst, n);
+    x.load(src, t, n);
+    y.store(dst, n);
   }
 }
 

@@ -806,6 +806,47 @@ void emit_group(CallPlan &c, std::vector<Fam> group, int level, int kind, std::v
   }
 }
 
+// How many of the first landing-ring chunks take their slots although the
+// copy kernel could read them straight into place: a read in place waits for
+// the preparation of the descriptors and for the levels up to its gate, a
+// slot is free at once and costs a second pass over the bytes in HBM.  Both
+// ways are timed with the rates they reach (57 GB/s on the link, kTailRate in
+// HBM, a launch 8 us, the preparation 20 ns a descriptor); a slot has to gain
+// 1 %.  us a KV call in place, all reads gated / the first chunk in its slot:
+// 6358 descriptors, 40 MB in 1820 / 1740; 22380, 137 MB 6700 / 6450; 4598,
+// 9 MB 880 / 820.
+int choose_slot_chunks(const CallPlan &c) {
+  constexpr double kLink = 57e9, kLaunch = 8e-6, kPrepare = 20e-9;
+  std::vector<double> done(size_t(c.n_levels), 0);
+  double levels = kLaunch + kPrepare * double(c.fams.size());
+  const double prepared = levels;
+  for (const Launch &L : c.levels) done[size_t(L.level)] = levels += kLaunch + 2 * double(L.bytes) / kTailRate;
+  auto time = [&](int m) {
+    double link = 0, scatter = levels;
+    for (int i = 0; i < m; ++i) {
+      const double bytes = double(c.chunks[size_t(i)].copies[0].bytes);
+      link += bytes / kLink;
+      scatter = std::max(scatter, link) + kLaunch + 2 * bytes / kTailRate;
+    }
+    for (const Launch &L : c.chunk_reads)
+      if (L.chunk >= m) link = std::max(link, L.gate < 0 ? prepared : done[size_t(L.gate)]) + double(L.bytes) / kLink;
+    return std::max(link, scatter);
+  };
+  int best = 0;
+  double t_best = time(0);
+  for (int m = 1; m <= std::min(int(c.chunks.size()), c.n_slots); ++m) {
+    const Chunk &ch = c.chunks[size_t(m) - 1];
+    // k_copy_linear reads one run of 16-byte chunks
+    if (ch.copies.size() != 1 || ch.copies[0].host_off % 16 || ch.copies[0].bytes % 16) break;
+    const double t = time(m);
+    if (t < 0.99 * t_best) {
+      best = m;
+      t_best = t;
+    }
+  }
+  return best;
+}
+
 void schedule(Plan &P, CallPlan &c, std::vector<Fam> &retained, std::vector<Pending> &inflow,
               std::vector<Pending> &outbound, bool kvcall) {
   int64_t live_hint = kvcall ? P.kv.live_blocks : INT64_MAX;
@@ -1436,6 +1477,7 @@ void schedule(Plan &P, CallPlan &c, std::vector<Fam> &retained, std::vector<Pend
       group.clear();
       bytes = 0;
     }
+    c.slot_chunks = choose_slot_chunks(c);
   }
 
   // ---- staging layout ------------------------------------------------------------------

@@ -104,6 +104,9 @@ struct CallPlan {
   // the chunks' scatters once more, as launches that read the pinned inflow
   // buffer beside the levels instead, in the order of their gates
   std::vector<Launch> chunk_reads;
+  // The first chunks, each in a slot of its own, that land there even from a
+  // pinned buffer, since their reads would have to wait for late levels.
+  int slot_chunks = 0;
   std::vector<HostCopy> outbound;
   std::vector<int> out_order;   // outbound issue order (by the level needing it)
   // Inflow other than large contiguous gaps is read by the copy kernel

@@ -47,7 +47,7 @@ def run(case):
     c = configs.get(case["w"], inplace=case["inplace"])
     if case.get("layers"):
         c["layers"] = case["layers"]
-    c.update(case.get("shape", {}))
+    c.update(case.get("shape", {}), inplace=case["inplace"])
     table, pool = pagetable.make_for(c)
     n_live = len(np.unique(table[table >= 0]))
     inplace = bool(c["inplace"])
@@ -65,7 +65,8 @@ def run(case):
     if case.get("split_kv_inflow"):
         mock.mock_split_host(C.c_void_p(hin_k))
     hout_w, hout_k = hmalloc(st.outbound_w), hmalloc(st.outbound_kv)
-    s0, s1 = stream(), stream()
+    s0 = stream()
+    s1 = s0 if case.get("one_stream") else stream()
     if case["warmup"]:
         atp.warmup(s0, s1, 256)
     files = names = None
@@ -111,7 +112,7 @@ def run(case):
     log = {}
     if case.get("log"):
         mock.mock_log.restype = C.c_char_p
-        roles = {s0: "compute", s1: "copy"}
+        roles = {s1: "copy", s0: "compute"}
         log = {"log": [(n, int(k), roles.get(int(s), "side")) for n, k, s in
                        (x.split() for x in mock.mock_log().decode().splitlines())]}
     return {"ok": True, **log, "launches": launches, "mock_launches": int(mock.mock_launches()),

@@ -53,6 +53,18 @@ def squeezed_ring_cfg():
                        self_old=2, n_seq=64, seq_tokens=2048, w_kind=KIND_TAG16, kv_kind=KIND_TAG16)
 
 
+def late_gates_cfg(**kw):
+    """A tiny decoder, TP 3 -> 2, whose KV shard of a fragmented pool moves
+    within itself in place: thousands of single-block copies in one level,
+    which every inflow byte has to wait for."""
+    from synth import configs
+    from synth.content import KIND_TAG16
+    shape = dict(layers=1, hidden=256, n_q=32, n_kv=4, head_dim=64, ffn=512, old_tp=3, new_tp=2, failed=[0],
+                 self_old=1, new_q_widths=None, new_ffn_widths=None, n_seq=13, seq_tokens=6016, block_tokens=32,
+                 fragmented=True, pool_factor=1.3, w_kind=KIND_TAG16, kv_kind=KIND_TAG16)
+    return configs.get(1, **{**shape, **kw})
+
+
 def say(msg):
     print(msg, flush=True)
     sys.stdout.flush()

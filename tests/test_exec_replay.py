@@ -12,6 +12,8 @@ import sys
 
 import pytest
 
+from tests.gpu_harness import late_gates_cfg
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 
 
@@ -88,6 +90,26 @@ def test_in_place_kv_reads_of_lines_that_cross_waves(mockhip, layout, head_dim, 
     r, = _replay(mockhip, [case])
     reads = [(n, g) for n, g, stream in r["log"] if stream == "copy" and "k_copy" in n]
     assert reads and all(kernel in n and g == groups for n, g in reads), reads
+
+
+def test_in_place_kv_inflow_with_late_gates_goes_to_its_slots(mockhip):
+    """Where every read in place would wait for the preparation of thousands
+    of descriptors and for a level, the first chunks are read into their slots
+    at once and scattered after the levels; with few descriptors the reads go
+    straight into place, and with one stream for both none holds up the
+    levels."""
+    late, few = late_gates_cfg(), late_gates_cfg(fragmented=False, pool_factor=1.0, n_seq=1, seq_tokens=64)
+    r = {}
+    for name, c in (("late", late), ("few", few), ("one-stream", late)):
+        case = {"w": 1, "inplace": True, "order": "weights-first", "steps": 1, "warmup": False, "log": True,
+                "shape": c, "one_stream": name == "one-stream"}
+        r[name], = _replay(mockhip, [case])
+        assert r[name]["ok"]
+    kinds = {k: [n for n, g, s in v["log"] if n != "copy"] for k, v in r.items()}
+    linear = [i for i, n in enumerate(kinds["late"]) if "k_copy_linear" in n]
+    prepares = [i for i, n in enumerate(kinds["late"]) if "k_prepare" in n]
+    assert linear and linear[0] < prepares[-1]  # before the KV call's own preparation
+    assert not any("k_copy_linear" in n for n in kinds["few"] + kinds["one-stream"])
 
 
 def test_async_load_with_the_kv_call_between(mockhip, tmp_path):

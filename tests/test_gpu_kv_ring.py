@@ -1,5 +1,6 @@
 """The in-place KV inflow chunk by chunk: read by the copy kernel from a
-pinned inflow buffer, and through the landing ring from pageable memory or a
+pinned inflow buffer into place or, where it would wait for late levels,
+into its slot, and through the landing ring from pageable memory or a
 buffer the kernel cannot read (not 256-byte aligned), with chunks of one and
 of several copies, against the oracle.  GPU, through the C ABI."""
 import numpy as np
@@ -9,7 +10,7 @@ import torch
 from paper_2511_11617_amd import atp
 from synth import configs
 from synth.content import KIND_RAW16
-from tests.gpu_harness import SQUEEZED_RING_CAP, squeezed_ring_cfg
+from tests.gpu_harness import SQUEEZED_RING_CAP, late_gates_cfg, squeezed_ring_cfg
 from tests.test_zz_no_alloc import _KV
 
 pytestmark = pytest.mark.gpu
@@ -28,11 +29,14 @@ def _ragged(head_dim):
 
 
 @pytest.mark.parametrize("memory", ["pinned", "pageable", "misaligned"])
-@pytest.mark.parametrize("name", ["ring-of-16-chunks", "odd-pieces", "one-odd-head", "wide-lines"])
+@pytest.mark.parametrize("name", ["ring-of-16-chunks", "odd-pieces", "one-odd-head", "late-gates",
+                                  "late-gates-four-slots", "wide-lines"])
 def test_in_place_kv_inflow(name, memory):
     cfg, cap = {"ring-of-16-chunks": (squeezed_ring_cfg(), SQUEEZED_RING_CAP),
                 "odd-pieces": (_ragged(7), 1 << 30),
                 "one-odd-head": (dict(_ragged(20), layers=1), 1 << 30),
+                "late-gates": (late_gates_cfg(), 1 << 30),
+                "late-gates-four-slots": (late_gates_cfg(layers=2), 24 << 20),
                 "wide-lines": (configs.scaled(5, layers=2, n_seq=2, seq_tokens=1024, kv_kind=KIND_RAW16),
                                1 << 30)}[name]
     k = _KV(cfg, atp.INPLACE, staging_cap=cap)
