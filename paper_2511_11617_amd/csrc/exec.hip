@@ -360,6 +360,13 @@ void check_kernel_host_buffer(const void *p, uint64_t bytes, const char *what) {
                                 "(the copy kernel accesses it directly)");
 }
 
+// Descriptors above which a copy command takes them to the device: below,
+// k_prepare's own reads of the pinned buffer cost less than the command.  The
+// one workgroup reads 96 KB per 3-4 us, much less beside an inflow that keeps
+// the link busy: us a KV call in place with the command / without, 390 and
+// 1165 descriptors equal, 4598 826 / 856, 8022 880 / 987.
+constexpr size_t kUploadDescs = 1024;
+
 void build_descs(Exec &E, const CallPlan &c, CallState &cs) {
   size_t n = c.fams.size();
   if (cs.desc_host) return;  // the descriptors of a plan never change
@@ -921,7 +928,12 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
 
   // ---- prepare: descriptors into staging, block list, tile counts ------------------
   PrepArgs pa{};
-  pa.plan_descs = cs.desc_host;
+  if (c.fams.size() > kUploadDescs) {
+    HIPCHK(hipMemcpyAsync(dev_desc, cs.desc_host, c.fams.size() * sizeof(Desc), hipMemcpyHostToDevice, compute));
+    is.other(compute);
+  } else {
+    pa.plan_descs = cs.desc_host;
+  }
   pa.descs = dev_desc;
   pa.n_desc = int32_t(c.fams.size());
   pa.kv = kvcall;

@@ -73,7 +73,7 @@ __device__ T block_exclusive_scan(T v, T *lds16, T *total) {
 }
 
 struct PrepArgs {
-  const Desc *plan_descs;  // the plan's descriptors, in pinned host memory
+  const Desc *plan_descs;  // the plan's descriptors, in pinned host memory (null: already in descs)
   Desc *descs;             // their device copies, block ranges resolved
   int32_t n_desc;
   int32_t kv;            // 1: compact the block table first
@@ -120,7 +120,7 @@ __device__ __forceinline__ void mark_blocks(const PrepArgs &a, int64_t e, int64_
 }
 
 // One workgroup, bound by the latency of its loads and by what one CU moves.
-// It reads the descriptors from the host's pinned copy and writes the error
+// It reads few descriptors from the host's pinned copy and writes the error
 // word there itself: a copy command before it and one at the call's end cost
 // the stream a blit kernel each (2-4 us and the gaps beside them) and the
 // host two more calls; a TP 4->3 KV move of 84 MB took 87 us a call
@@ -147,7 +147,7 @@ __global__ void __launch_bounds__(kPrepThreads) k_prepare(PrepArgs a) {
   if (tid == 0) s_err = 0;
   // (the loops below read descs only after a barrier)
   constexpr int kDescLoads = 4;
-  const int64_t words = int64_t(a.n_desc) * int64_t(sizeof(Desc) / 16);
+  const int64_t words = a.plan_descs ? int64_t(a.n_desc) * int64_t(sizeof(Desc) / 16) : 0;
   for (int64_t i0 = tid; i0 < words; i0 += nt * kDescLoads) {
     u32x4 v[kDescLoads];
 #pragma unroll

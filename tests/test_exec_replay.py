@@ -112,6 +112,15 @@ def test_in_place_kv_inflow_with_late_gates_goes_to_its_slots(mockhip):
     assert not any("k_copy_linear" in n for n in kinds["few"] + kinds["one-stream"])
 
 
+def test_many_descriptors_go_to_the_device_by_a_copy_command(mockhip):
+    case = {"w": 1, "inplace": True, "order": "weights-first", "steps": 1, "warmup": False, "log": True}
+    many, few = _replay(mockhip, [dict(case, shape=late_gates_cfg()), dict(case, shape=late_gates_cfg(
+        fragmented=False, pool_factor=1.0, n_seq=1, seq_tokens=320))])
+    copies = [g for n, g, s in many["log"] if n == "copy" and s == "compute"]
+    assert len(copies) == 1 and copies[0] > 96 * 1024  # the KV call's 6358 descriptors; the weights call has few
+    assert not [g for n, g, s in few["log"] if n == "copy" and s == "compute"]
+
+
 def test_async_load_with_the_kv_call_between(mockhip, tmp_path):
     """atp_load_reshard_weights_async, the KV call while the reads run, then
     atp_sync issuing the weight pieces: in and out of place, fresh plans in
