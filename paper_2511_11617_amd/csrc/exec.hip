@@ -496,6 +496,13 @@ constexpr double kRepackRate = 6000;
 // flight, on 20 / 24 / 28 / 32 workgroups 7880 / 7550 / 7530 / 7535 and 9450 /
 // 9180 / 9240 / 9440; through the landing ring 7550 and 9275.
 constexpr LinkGrid kHostReadAcross = {24, 10, 32, true};
+// In-place KV reads beside the call's outbound copies, which the runtime runs
+// as wide blit kernels: with more reads in flight the blits stand still until
+// the reads are done, with these both go on.  us a KV call of 105 MB in and 105
+// out / 17 MB in and out with 16 / 20 / 24 / 32 workgroups, one narrow tile each:
+// 2790 / 2320 / 2990 / 3520 and 473 / 464 / 615 / 670 (wide tiles on 10: 3540,
+// through the landing ring's copies 2385 and 465).
+constexpr LinkGrid kHostReadBesideBlit = {20, 5, 20, false};
 // The outbound reads get a narrow grid: wide device-to-host writers (the
 // runtime's 512-workgroup blits) slowed a concurrent HBM-bound repack
 // several-fold; 64 KiB in flight leave a concurrent HBM copy at full speed
@@ -560,6 +567,7 @@ struct Issuer {
   int64_t *dev_prefix;
   int32_t *dev_live;
   hipStream_t copy;
+  uint64_t beside_out;  // inflow bytes that land beside the KV call's outbound copies
   std::map<hipStream_t, hipEvent_t> mark;
 
   void other(hipStream_t st) { mark.erase(st); }
@@ -608,6 +616,8 @@ struct Issuer {
     });
     cs.h2d_bytes += L.bytes;
   }
+  // whether the next `bytes` land beside the outbound copies, by their middle
+  bool is_beside(uint64_t bytes) const { return cs.h2d_bytes + bytes / 2 < beside_out; }
   // a landing-ring chunk read the same way: its scatter's descriptors address
   // the slot, so the base moves until the slot's bytes are the chunk's bytes
   // of the inflow buffer
@@ -616,10 +626,21 @@ struct Issuer {
     for (int d = L.d0; d < L.d1; ++d) across = across || !whole_waves(c.fams[size_t(d)]);
     const LinkGrid &grid = across ? kHostReadAcross : read_grid;
     char *base = reinterpret_cast<char *>(reinterpret_cast<uintptr_t>(host_in) + h.host_off - h.dev_off);
-    timed(4, -1, L.bytes, s, [&] {
-      launch_copy(L, dev_desc, dev_prefix, nullptr, b_out, base, dev_live, s, &grid);
-    });
-    cs.h2d_bytes += L.bytes;
+    // cut where the outbound copies will be done
+    Launch piece = L;
+    for (int d = L.d0; d < L.d1; piece.d0 = d) {
+      const bool beside = is_beside(c.fams[size_t(d)].bytes());
+      piece.bytes = 0;
+      do {
+        piece.bytes += c.fams[size_t(d)].bytes();
+        cs.h2d_bytes += c.fams[size_t(d)].bytes();
+      } while (++d < L.d1 && is_beside(c.fams[size_t(d)].bytes()) == beside);
+      piece.d1 = d;
+      timed(4, -1, piece.bytes, s, [&] {
+        launch_copy(piece, dev_desc, dev_prefix, nullptr, b_out, base, dev_live, s,
+                    beside ? &kHostReadBesideBlit : &grid);
+      });
+    }
   }
   // a landing-ring chunk into its slot, at once; returns its end mark
   hipEvent_t slot_read(const HostCopy &h, hipStream_t s) {
@@ -879,8 +900,15 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
   const LinkGrid &read_grid = do_out && !kvcall && !await && !kv_covers ? kHostReadBesideOutbound
                               : t_repack >= 0.25 * t_reads ? kHostReadBesideRepack
                                                            : kHostRead;
+  // The first of an in-place KV call's inflow bytes land beside its outbound
+  // copies, as many as those copy (both directions run at about the same
+  // rate); with the weights call pending, whose traffic holds the copies up
+  // too, all of them: its call and a KV call of 110 MB in and 41 out took 2960
+  // us with the first 41 MB read so, 2540 with all (279 MB in, 104 out: 5450,
+  // 4780).
+  const uint64_t beside_out = !kvcall || !do_out ? 0 : E.w.pending ? UINT64_MAX : c.outbound_bytes;
   Issuer is{E, cs, c, kvcall ? P.kv.num_blocks : 0, kvcall ? P.kv.live_blocks : 0, b_out, b_st, host_in, read_grid,
-            dev_desc, dev_prefix, dev_live, copy, {}};
+            dev_desc, dev_prefix, dev_live, copy, beside_out, {}};
   cs.compute = compute;
   cs.copy = copy;
   cs.finish_issue = nullptr;

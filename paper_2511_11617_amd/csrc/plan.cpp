@@ -759,7 +759,7 @@ constexpr uint64_t kJoinMax = 8ull << 20;
 
 // Emit launches for a group of families: aligned ones first (with wide
 // tiles, if `allow_wide`, for short KV lines; a landing-ring chunk's only where
-// they make whole waves, see kHostReadAcross), then the ones that are not.
+// they make whole waves and nothing goes out beside them), then the ones that are not.
 // Families are appended to c.fams; every family of a launch has the same
 // DF_ALIGNED and DF_WIDE flags.
 void emit_group(CallPlan &c, std::vector<Fam> group, int level, int kind, std::vector<Launch> &out,
@@ -1379,7 +1379,7 @@ void schedule(Plan &P, CallPlan &c, std::vector<Fam> &retained, std::vector<Pend
       if (pieces.empty()) return;
       ch.slot = next_slot;
       next_slot = (next_slot + 1) % c.n_slots;
-      emit_group(c, pieces, -1, 2, ch.scatters, live_hint, true);
+      emit_group(c, pieces, -1, 2, ch.scatters, live_hint, outbound.empty());
       c.chunks.push_back(ch);
       pieces.clear();
       ch = Chunk();
@@ -1477,7 +1477,8 @@ void schedule(Plan &P, CallPlan &c, std::vector<Fam> &retained, std::vector<Pend
       group.clear();
       bytes = 0;
     }
-    c.slot_chunks = choose_slot_chunks(c);
+    // beside outbound copies the reads are held back, and a slot gains nothing
+    if (outbound.empty()) c.slot_chunks = choose_slot_chunks(c);
   }
 
   // ---- staging layout ------------------------------------------------------------------

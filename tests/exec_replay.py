@@ -3,7 +3,7 @@ libatp.so with the HIP runtime replaced by tests/mockhip (preloaded), and
 prints one line per case.  No torch, no GPU.
 
 argv: a JSON list of cases {"w": workload, "inplace": bool, "order":
-"weights-first" | "kv-first" | "async-load", "steps": n, "warmup": bool,
+"weights-first" | "kv-first" | "kv-only" | "async-load", "steps": n, "warmup": bool,
 "layers": optional layer count, "shape": optional changes of the workload's
 shape, "log": whether to return the last step's launches and copies}.
 "async-load" reads the weight inflow from a checkpoint of holes
@@ -91,7 +91,9 @@ def run(case):
                          s0, s1)
 
         try:
-            if case["order"] == "kv-first":
+            if case["order"] == "kv-only":
+                kcall()
+            elif case["order"] == "kv-first":
                 kcall()
                 wcall()
             elif case["order"] == "async-load":

@@ -112,6 +112,24 @@ def test_in_place_kv_inflow_with_late_gates_goes_to_its_slots(mockhip):
     assert not any("k_copy_linear" in n for n in kinds["few"] + kinds["one-stream"])
 
 
+@pytest.mark.parametrize("order", ["kv-only", "weights-first"])
+def test_in_place_kv_reads_beside_outbound_copies_are_held_back(mockhip, order):
+    """An in-place KV call that copies bytes out reads as many bytes of its
+    inflow with a grid that leaves the copies their share of the link, all of
+    them with the weights call pending, and the rest with the usual one."""
+    shape = dict(late_gates_cfg(n_q=16, n_kv=8, head_dim=80, layers=4, fragmented=False, pool_factor=1.0,
+                                block_tokens=16), new_kv_widths=[4, 4], kv_rule="widths")
+    r, = _replay(mockhip, [{"w": 1, "inplace": True, "order": order, "steps": 1, "warmup": False, "log": True,
+                            "shape": shape}])
+    log = [x for x in r["log"] if x[2] == "copy" or x[0] == "copy"]
+    out = sum(g for n, g, s in log if n == "copy" and s == "side")
+    reads = [(n, g) for n, g, s in log if s == "copy" and "k_copy" in n]
+    assert out > 0 and not any("linear" in n for n, g in reads)
+    held = [("k_copy16ILi2" in n and g == 20) for n, g in reads]
+    assert held[0] and held == sorted(held, reverse=True)
+    assert all(held) if order == "weights-first" else not held[-1]
+
+
 def test_many_descriptors_go_to_the_device_by_a_copy_command(mockhip):
     case = {"w": 1, "inplace": True, "order": "weights-first", "steps": 1, "warmup": False, "log": True}
     many, few = _replay(mockhip, [dict(case, shape=late_gates_cfg()), dict(case, shape=late_gates_cfg(
