@@ -77,6 +77,10 @@ struct CallState {
   std::function<void()> finish_issue;
 };
 
+// A weights call's word, on a line of its own beside the error word, that is
+// set once the KV call is issued too.
+int32_t *calm_word(CallState &w) { return w.err_host + 32; }
+
 // Process-wide recycling of HIP objects per device.  Each plan owns what it
 // takes until it is freed; creating events, streams and pinned buffers for
 // every plan would otherwise cost tens of milliseconds per reshard.
@@ -512,9 +516,11 @@ constexpr LinkGrid kOutbound = {4, 2, 8, true};
 // Beside host reads, the outbound writes share the link's upstream direction
 // with the reads' requests and slow the reads: the 4-layer TP 8->7 reshard in
 // place took 55.5 / 54.1 / 51.4 / 51.1 ms a step with 16 / 8 / 5 / 4 workgroups
-// of one tile.  Half of kOutbound is enough where the KV inflow, at kLinkRate,
-// outlasts the outbound reads, at the kOutboundRate they reach beside it (GB/s).
-constexpr LinkGrid kOutboundBesideReads = {2, 1, 4, true};
+// of one tile.  Half the rate is enough where the KV inflow, at kLinkRate,
+// outlasts the outbound reads, at the kOutboundRate they reach beside it (GB/s):
+// the KV call then sets the word that makes the pending weights call's outbound
+// launches calm.  (A weights call alone on that plan took 33.9 ms with half the
+// workgroups from the start, and takes 23.4.)
 constexpr double kOutboundRate = 22, kLinkRate = 57;
 // The weight inflow read beside kOutbound: fewer reads in flight leave the
 // writes more of the upstream direction.  ms for the weights of the 4-layer
@@ -524,18 +530,18 @@ constexpr double kOutboundRate = 22, kLinkRate = 57;
 constexpr LinkGrid kHostReadBesideOutbound = {24, 10, 24, false};
 
 void launch_copy(const Launch &L, const Desc *dev_desc, const int64_t *dev_prefix, char *b0, char *b1, char *b2,
-                 const int32_t *live, hipStream_t s, const LinkGrid *link = nullptr) {
+                 const int32_t *live, hipStream_t s, const LinkGrid *link = nullptr, const int32_t *calm = nullptr) {
   // one workgroup per tile, or a narrow persistent grid over the link (the
   // kernels loop over the tiles of the launch)
   const uint64_t cap = !link ? uint64_t(1) << 30 : !L.aligned ? link->any : L.wide ? link->wide : link->narrow;
   const dim3 g(unsigned(std::min<uint64_t>(std::max<uint64_t>(L.tiles_max, 1), cap)));
-  auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, g, dim3(kThreads), 0, s, dev_desc, dev_prefix, L.d0, L.d1, b0, b1, b2, live);
+  auto go = [&](auto kernel, auto... more) {
+    hipLaunchKernelGGL(kernel, g, dim3(kThreads), 0, s, dev_desc, dev_prefix, L.d0, L.d1, b0, b1, b2, live, more...);
   };
   if (!L.aligned)
-    go(k_copy_any);
+    go(k_copy_any, calm);
   else if (link && (L.wide || link->two))
-    L.wide ? go(k_copy_link<kWideUnroll>) : go(k_copy_link<kUnroll>);
+    L.wide ? go(k_copy_link<kWideUnroll>, calm) : go(k_copy_link<kUnroll>, calm);
   else
     L.wide ? go(k_copy16<kWideUnroll>) : go(k_copy16<kUnroll>);
   HIPCHK(hipGetLastError());
@@ -874,6 +880,10 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
     cs.err_host = static_cast<int32_t *>(E.pinned(256, &cap));
   }
   *cs.err_host = 0;
+  if (!kvcall)
+    __atomic_store_n(calm_word(cs), 0, __ATOMIC_RELAXED);
+  else if (P.inplace && E.w.pending && c.inflow)
+    __atomic_store_n(calm_word(E.w), 1, __ATOMIC_RELAXED);
   cs.old_arena = my_old;
   cs.new_arena = my_new;
   cs.staging = my_st;
@@ -1006,7 +1016,7 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
   // That work and the weight inflow read after it stay off the caller's
   // streams, so that they do not hold up the other call's work queued
   // behind them.
-  const LinkGrid &out_grid = kv_covers ? kOutboundBesideReads : kOutbound;
+  const int32_t *calm = kv_covers ? calm_word(cs) : nullptr;
   size_t issued = 0;  // outbound pieces read out so far, in plan order
   const bool split = do_out && !kvcall;
   hipStream_t late_comp = compute;
@@ -1068,7 +1078,7 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
       }
       L.d1 = c.out_d0 + int(issued);
       const CallState::LaunchRec r = is.timed(3, -1, L.bytes, late_comp, [&] {
-        launch_copy(L, dev_desc, dev_prefix, b_in, host_out, b_st, dev_live, late_comp, &out_grid);
+        launch_copy(L, dev_desc, dev_prefix, b_in, host_out, b_st, dev_live, late_comp, &kOutbound, calm);
       });
       if (!cs.d2h0) cs.d2h0 = r.e0;
       cs.d2h1 = r.e1;

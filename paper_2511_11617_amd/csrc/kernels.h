@@ -473,6 +473,25 @@ __device__ __forceinline__ void store16_any(char *p, u32x4 v) {
   __builtin_nontemporal_store(v, (global_u32x4_any *)(p));
 }
 
+// Whether a launch is to go at half its rate: a word in pinned host memory
+// (null: no), looked at every kCalmTiles tiles.  Each wave decides for itself.
+constexpr uint32_t kCalmTiles = 32;
+struct Calm {
+  const int32_t *word;
+  uint32_t n = 0;
+  int32_t now = 0, seen = 0;
+
+  __device__ __forceinline__ explicit Calm(const int32_t *w) : word(w) {}
+  __device__ __forceinline__ bool poll() {
+    if (word && n++ % kCalmTiles == 0) {
+      now = seen;  // the read before this one: it has long arrived
+      seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      if (n == 1) now = seen;
+    }
+    return now != 0;
+  }
+};
+
 // Lines [c0, c1] shorter than one chunk, one per lane, byte by byte.
 __device__ __forceinline__ void copy_short_lines(const Desc &x, uint64_t c0, uint64_t c1, char *b0, char *b1, char *b2,
                                                  const int32_t *__restrict__ live) {
@@ -484,8 +503,10 @@ __device__ __forceinline__ void copy_short_lines(const Desc &x, uint64_t c0, uin
 
 __global__ void __launch_bounds__(kThreads) k_copy_any(const Desc *__restrict__ descs,
                                                        const int64_t *__restrict__ prefix, int d0, int d1, char *b0,
-                                                       char *b1, char *b2, const int32_t *__restrict__ live) {
+                                                       char *b1, char *b2, const int32_t *__restrict__ live,
+                                                       const int32_t *calm) {
   constexpr int U = kUnroll;
+  Calm slow(calm);
   const int64_t T0 = prefix[d0], T1 = prefix[d1];
   for (int64_t t = T0 + tile_of_block(); t < T1; t += gridDim.x) {
     const int d = find_desc(prefix, d0, d1, t);
@@ -493,6 +514,7 @@ __global__ void __launch_bounds__(kThreads) k_copy_any(const Desc *__restrict__ 
     const uint64_t total = uint64_t(x.o_end - x.o_begin) * x.rows * x.cpl;
     const uint64_t cbase = uint64_t(t - prefix[d]) * kTileChunks;
     const uint64_t clast = (cbase + kTileChunks < total ? cbase + kTileChunks : total) - 1;
+    if (slow.poll()) __builtin_amdgcn_s_sleep(55);  // about the time a tile takes on 8 workgroups over the link
     if (x.run < 16) {
       copy_short_lines(x, cbase, clast, b0, b1, b2, live);
       continue;
@@ -517,7 +539,7 @@ __global__ void __launch_bounds__(kThreads) k_copy_any(const Desc *__restrict__ 
 // registers of their own (moving one into the other would wait for its
 // loads).  The 40-layer TP 8->7 last rank's 374 MB came in at 48 GB/s beside
 // its repack with one tile in flight on 32 workgroups, 57 with two on 20:
-// the step took 7.33 ms and takes 6.63.
+// the step took 7.33 ms and takes 6.63.  A calm launch keeps one tile in flight.
 template <int U>
 struct LinkTile {
   u32x4 v[U];
@@ -544,17 +566,24 @@ struct LinkTile {
 template <int U>
 __global__ void __launch_bounds__(kThreads) k_copy_link(const Desc *__restrict__ descs,
                                                         const int64_t *__restrict__ prefix, int d0, int d1, char *b0,
-                                                        char *b1, char *b2, const int32_t *__restrict__ live) {
+                                                        char *b1, char *b2, const int32_t *__restrict__ live,
+                                                        const int32_t *calm) {
   const int64_t T1 = prefix[d1];
   int64_t t = prefix[d0] + tile_of_block();
   if (t >= T1) return;
   int d = find_desc(prefix, d0, d1, t);
+  Calm one(calm);
   LinkTile<U> x, y;
   x.load(descs[d], t - prefix[d], b0, b1, b2, live);
   for (;;) {
     t += gridDim.x;
     if (t >= T1) return x.store();
     while (prefix[d + 1] <= t) ++d;  // a workgroup's tiles come in order
+    if (one.poll()) {
+      x.store();
+      x.load(descs[d], t - prefix[d], b0, b1, b2, live);
+      continue;
+    }
     y.load(descs[d], t - prefix[d], b0, b1, b2, live);
     x.store();
     t += gridDim.x;

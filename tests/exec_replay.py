@@ -3,7 +3,8 @@ libatp.so with the HIP runtime replaced by tests/mockhip (preloaded), and
 prints one line per case.  No torch, no GPU.
 
 argv: a JSON list of cases {"w": workload, "inplace": bool, "order":
-"weights-first" | "kv-first" | "kv-only" | "async-load", "steps": n, "warmup": bool,
+"weights-first" | "kv-first" | "kv-only" |
+"weights-only" | "async-load", "steps": n, "warmup": bool,
 "layers": optional layer count, "shape": optional changes of the workload's
 shape, "log": whether to return the last step's launches and copies}.
 "async-load" reads the weight inflow from a checkpoint of holes
@@ -93,6 +94,8 @@ def run(case):
         try:
             if case["order"] == "kv-only":
                 kcall()
+            elif case["order"] == "weights-only":
+                wcall()
             elif case["order"] == "kv-first":
                 kcall()
                 wcall()

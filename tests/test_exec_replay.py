@@ -130,6 +130,15 @@ def test_in_place_kv_reads_beside_outbound_copies_are_held_back(mockhip, order):
     assert all(held) if order == "weights-first" else not held[-1]
 
 
+def test_outbound_reads_of_a_weights_call_alone_get_their_whole_grid(mockhip):
+    """The plan describes a KV cache whose inflow would outlast the weights'
+    outbound reads, but whether the KV call is made is not known yet."""
+    r, = _replay(mockhip, [{"w": 5, "inplace": True, "order": "weights-only", "steps": 1, "warmup": False, "layers": 2,
+                            "log": True, "shape": {"n_seq": 32}}])
+    side = [(n, g) for n, g, s in r["log"] if s == "side" and "k_copy" in n]
+    assert {g for n, g in side if "k_copy_linkILi2" in n} == {4}, side
+
+
 def test_many_descriptors_go_to_the_device_by_a_copy_command(mockhip):
     case = {"w": 1, "inplace": True, "order": "weights-first", "steps": 1, "warmup": False, "log": True}
     many, few = _replay(mockhip, [dict(case, shape=late_gates_cfg()), dict(case, shape=late_gates_cfg(
