@@ -27,6 +27,9 @@ uint64_t __ballot(int);
 inline int __popcll(uint64_t v) { return __builtin_popcountll(v); }
 int atomicOr(int *, int);
 
+#define __HIP_MEMORY_SCOPE_SYSTEM 0
+#define __hip_atomic_load(p, order, scope) (*(p))
+#define __builtin_amdgcn_s_sleep(n) ((void)(n))
 #define __builtin_amdgcn_readfirstlane(x) (x)
 #define __builtin_amdgcn_mbcnt_lo(m, v) (v)
 #define __builtin_amdgcn_mbcnt_hi(m, v) (v)
