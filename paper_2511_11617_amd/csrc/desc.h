@@ -69,6 +69,10 @@ constexpr uint32_t line_chunks(uint64_t run, uint32_t flags) {
   return uint32_t((flags & DF_ALIGNED) ? run >> 4 : run < 16 ? 1 : (run + 30) >> 4);
 }
 
+// Bytes of a flag per block id, in whole groups of 64; the live-block list has
+// room for four times as many.
+constexpr int64_t flag_room(int64_t n_blocks) { return (n_blocks + 63) / 64 * 64; }
+
 struct alignas(16) Desc {
   uint64_t src_off, dst_off;
   uint64_t src_pitch, dst_pitch;

@@ -27,6 +27,8 @@
 namespace atp {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef u32x4 __attribute__((address_space(1))) global_u32x4;
+typedef unsigned char __attribute__((address_space(1))) global_u8;
 
 enum : int32_t { ERR_BAD_BLOCK = 1, ERR_LIVE_COUNT = 2 };
 
@@ -95,16 +97,15 @@ __device__ __forceinline__ int64_t live_rank(const PrepArgs &a, int64_t b, int64
   return a.rank[b >> 6] + __popcll(a.mask[b >> 6] & ((uint64_t(1) << (b & 63)) - 1));
 }
 
-// Block ids one pass of k_prepare marks: a byte each in LDS.
+// Block ids k_prepare takes at once: a byte each in LDS.
 constexpr int kPrepWindow = 1 << 16;
 constexpr int kPrepThreads = 1024;
 constexpr int kPrepGroups = 8;  // groups of 64 ids in flight per wave
 
 // Table entries [e, e + 1024 K), K loads in flight per thread: marks the ids
-// in [w0, w0 + n) and keeps the largest id seen.
-template <int K>
-__device__ __forceinline__ void mark_blocks(const PrepArgs &a, int64_t e, int64_t w0, int n, uint8_t *flag,
-                                            int32_t *top) {
+// below n (in LDS or in memory) and keeps the largest id seen.
+template <int K, typename Flags>
+__device__ __forceinline__ void mark_blocks(const PrepArgs &a, int64_t e, int64_t n, Flags flag, int32_t *top) {
   int32_t v[K];
 #pragma unroll
   for (int k = 0; k < K; ++k) {
@@ -114,9 +115,33 @@ __device__ __forceinline__ void mark_blocks(const PrepArgs &a, int64_t e, int64_
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     *top = v[k] > *top ? v[k] : *top;
-    const uint32_t p = uint32_t(v[k]) - uint32_t(w0);  // an id of -1 or below lands past n
-    if (p < uint32_t(n)) flag[p] = 1;
+    if (v[k] >= 0 && v[k] < n) flag[v[k]] = 1;
   }
+}
+
+// The whole table.
+template <typename Flags>
+__device__ __forceinline__ void mark_table(const PrepArgs &a, int64_t n, Flags flag, int32_t *top) {
+  constexpr int nt = kPrepThreads;
+  int64_t e = 0;  // the widest batches first, then one as wide as the rest needs
+  for (; a.n_entries - e >= int64_t(nt) * 16; e += int64_t(nt) * 16) mark_blocks<16>(a, e, n, flag, top);
+  const int64_t rest = a.n_entries - e;
+  if (rest > nt * 8)
+    mark_blocks<16>(a, e, n, flag, top);
+  else if (rest > nt * 4)
+    mark_blocks<8>(a, e, n, flag, top);
+  else if (rest > nt)
+    mark_blocks<4>(a, e, n, flag, top);
+  else if (rest > 0)
+    mark_blocks<1>(a, e, n, flag, top);
+}
+
+// Flags of a pool beyond one window, a byte per id: the last quarter of the
+// live list's room.  The list grows 4 bytes per live id from the front, so
+// that after the ids below w it ends at most at 4 w, below the flags of the
+// ids from w on.
+__device__ __forceinline__ uint8_t *pool_flags(const PrepArgs &a) {
+  return reinterpret_cast<uint8_t *>(a.live) + 3 * flag_room(a.n_blocks);
 }
 
 // One workgroup, bound by the latency of its loads and by what one CU moves.
@@ -131,10 +156,10 @@ __device__ __forceinline__ void mark_blocks(const PrepArgs &a, int64_t e, int64_
 // table would queue up on the words of a bit mask, and random ids on the
 // cache lines of flags in memory).  Each wave then turns 64 bytes into a
 // mask with a ballot, one scan over the groups gives their ranks, and a wave
-// writes the ids of a group to consecutive places.  Pools beyond
-// kPrepWindow ids take several passes over the table.  64 / 18350 / 32768 /
-// 65536 / 262144 ids take 5 / 9 / 13 / 22 / 134 us; flags in memory and a run
-// of blocks per thread took 4 / 39 / 86 / 165 / 700.
+// writes the ids of a group to consecutive places.  A pool beyond kPrepWindow
+// ids is marked in memory in one pass over the table and taken window by window
+// from there (a pass over the table per window took longer from about the third
+// window on, and more the emptier the table is).
 __global__ void __launch_bounds__(kPrepThreads) k_prepare(PrepArgs a) {
   __shared__ int64_t s64[16];
   __shared__ int32_t s32[16];
@@ -164,22 +189,25 @@ __global__ void __launch_bounds__(kPrepThreads) k_prepare(PrepArgs a) {
   int64_t n_live = 0;
   if (a.kv) {
     int32_t top = -1;
+    const bool one_window = a.n_blocks <= kPrepWindow;
+    global_u8 *flags = (global_u8 *)pool_flags(a);
+    if (!one_window) {
+      for (int64_t i = tid; i < flag_room(a.n_blocks) / 16; i += nt) ((global_u32x4 *)flags)[i] = u32x4{0, 0, 0, 0};
+      __syncthreads();
+      mark_table(a, a.n_blocks, flags, &top);
+      __syncthreads();
+    }
     for (int64_t w0 = 0; w0 < a.n_blocks; w0 += kPrepWindow) {
       const int n = int(a.n_blocks - w0 < kPrepWindow ? a.n_blocks - w0 : kPrepWindow);
       const int groups = (n + 63) >> 6;
-      for (int i = tid; i < groups * 4; i += nt) reinterpret_cast<u32x4 *>(s_flag)[i] = u32x4{0, 0, 0, 0};
-      __syncthreads();
-      int64_t e = 0;  // the widest batches first, then one as wide as the rest needs
-      for (; a.n_entries - e >= int64_t(nt) * 16; e += int64_t(nt) * 16) mark_blocks<16>(a, e, w0, n, s_flag, &top);
-      const int64_t rest = a.n_entries - e;
-      if (rest > nt * 8)
-        mark_blocks<16>(a, e, w0, n, s_flag, &top);
-      else if (rest > nt * 4)
-        mark_blocks<8>(a, e, w0, n, s_flag, &top);
-      else if (rest > nt)
-        mark_blocks<4>(a, e, w0, n, s_flag, &top);
-      else if (rest > 0)
-        mark_blocks<1>(a, e, w0, n, s_flag, &top);
+      if (one_window) {
+        for (int i = tid; i < groups * 4; i += nt) reinterpret_cast<u32x4 *>(s_flag)[i] = u32x4{0, 0, 0, 0};
+        __syncthreads();
+        mark_table(a, n, s_flag, &top);
+      } else {
+        for (int i = tid; i < groups * 4; i += nt)
+          reinterpret_cast<u32x4 *>(s_flag)[i] = ((const global_u32x4 *)(flags + w0))[i];
+      }
       __syncthreads();
       for (int g = wave * kPrepGroups; g < groups; g += kPrepGroups * (nt >> 6)) {
         uint8_t f[kPrepGroups];
@@ -315,7 +343,6 @@ __device__ __forceinline__ LineAddr line_addr(const Desc &x, uint32_t line, char
 // the non-temporal hint by default.  The pointers are cast to the global
 // address space, which keeps the accesses global_* rather than flat_*
 // where the compiler cannot infer it.
-typedef u32x4 __attribute__((address_space(1))) global_u32x4;
 
 __device__ __forceinline__ u32x4 load16(const u32x4 *p) {
 #if ATP_NT_LOAD
@@ -464,7 +491,6 @@ __global__ void __launch_bounds__(kThreads) k_copy16(const Desc *__restrict__ de
 // 0.65 / 0.34 -> 4.8 / 3.2 / 2.7 TB/s at 306 / 124 / 71 MB.  Tiles of twice
 // the width, and source boundaries for the HBM copies, were 0-9 % slower.
 typedef u32x4 __attribute__((address_space(1), aligned(1))) global_u32x4_any;
-typedef unsigned char __attribute__((address_space(1))) global_u8;
 
 __device__ __forceinline__ u32x4 load16_any(const char *p) {
   return __builtin_nontemporal_load((const global_u32x4_any *)(p));

@@ -906,7 +906,7 @@ void schedule(Plan &P, CallPlan &c, std::vector<Fam> &retained, std::vector<Pend
       uint64_t ring_in = 0;
       for (const Pending &pd : inflow) ring_in += pd.fam.bytes();
       used += std::min<uint64_t>(kRingSlots * kRingSlotMax, align_up(ring_in, 256));
-      used += uint64_t(P.kv.num_blocks) * 12 + 1024;
+      used += uint64_t(P.kv.num_blocks) * 5 + 1024;
     }
     used += (uint64_t(nodes.size()) * 2 + outbound.size() + inflow.size() + 64) * (sizeof(Desc) + 8) + (1u << 20);
     tail_room = used < cap ? std::min<uint64_t>(cap - used, kTailMax) : 0;
@@ -1491,13 +1491,13 @@ void schedule(Plan &P, CallPlan &c, std::vector<Fam> &retained, std::vector<Pend
   c.off_prefix = at;
   at = align_up(at + (nd + 1) * 8, 256);
   if (kvcall) {
-    uint64_t nb = P.kv.num_blocks;
+    const uint64_t room = uint64_t(flag_room(P.kv.num_blocks)), groups = room / 64;
     c.off_kvmask = at;
-    at = align_up(at + nb * 4, 256);
+    at = align_up(at + groups * 8, 256);
     c.off_kvrank = at;
-    at = align_up(at + (nb + 1) * 4, 256);
+    at = align_up(at + groups * 4, 256);
     c.off_kvlive = at;
-    at = align_up(at + nb * 4, 256);
+    at = align_up(at + room * 4, 256);
   }
   c.off_ring = at;
   at += uint64_t(c.n_slots) * c.ring_slot;

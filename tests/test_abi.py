@@ -215,3 +215,12 @@ def test_old_widths_and_floor_rules_give_the_same_plan_as_explicit_ranges():
     p = b.plan()
     assert p.old_ranges(0) == [(0, 2), (2, 3), (3, 4), (4, 4)]
     assert p.old_ranges(1) == [(0, 1), (1, 2), (1, 2), (2, 2)]
+
+
+def test_block_lists_take_little_staging():
+    """The live list, masks and ranks of a pool take 4.2 bytes per block (what
+    is reserved counts against the no-allocation call's scratch array: a pool
+    of 15 million blocks fits)."""
+    c = configs.get(1)
+    small, large = (problem.build(c, n_live=64, pool=n).plan().stats().staging_kv for n in (64, 15_000_000))
+    assert large - small <= 15_000_000 * 4.2 and large <= atp.scratch_bytes()
