@@ -1484,8 +1484,6 @@ void schedule(Plan &P, CallPlan &c, std::vector<Fam> &retained, std::vector<Pend
   // ---- staging layout ------------------------------------------------------------------
   uint64_t nd = c.fams.size();
   uint64_t at = 0;
-  c.off_meta = at;
-  at += 256;
   c.off_desc = at;
   at = align_up(at + nd * sizeof(Desc), 256);
   c.off_prefix = at;

@@ -130,7 +130,7 @@ struct CallPlan {
   uint64_t retained = 0, moved = 0, staged = 0, tail = 0;
   uint64_t inflow = 0, outbound_bytes = 0;
   // staging layout
-  uint64_t off_meta = 0, off_desc = 0, off_prefix = 0, off_kvmask = 0,
+  uint64_t off_desc = 0, off_prefix = 0, off_kvmask = 0,
            off_kvrank = 0, off_kvlive = 0, off_ring = 0, off_stage = 0,
            ring_slot = 0, staging_need = 0;
   int n_slots = 0;
