@@ -662,9 +662,11 @@ struct Issuer {
   }
   void end_host_reads(hipStream_t s) { cs.hr1 = mark_or_record(s, true); }
   // While the inflow buffer is still being filled, the direct landings and
-  // the host reads (each launch cut at descriptor boundaries into pieces of
-  // at least kPipeBytes) are issued in the order of the end of the bytes
-  // they read, each once `await` says those bytes are in.
+  // the host reads are issued in the order of the end of the bytes they read,
+  // each once `await` says those bytes are in.  The launches' descriptors are
+  // cut into pieces of about kPipeBytes that read the buffer more or less in
+  // one place (in place a launch holds what gets ready together, which may lie
+  // gigabytes apart in the buffer): at most twice their bytes, or kPipeBytes.
   void awaited(hipStream_t s, const std::function<void(uint64_t)> &await) {
     struct Piece {
       uint64_t end;
@@ -674,23 +676,44 @@ struct Issuer {
     std::vector<Piece> pieces;
     for (const HostCopy &h : c.directs) pieces.push_back({h.host_off + h.bytes, &h, Launch{}});
     for (const Launch &L : c.host_reads) {
-      Launch piece = L;
-      piece.bytes = 0;
-      uint64_t end = 0;
+      Piece p{0, nullptr, L};
+      p.L.bytes = 0;
+      uint64_t begin = UINT64_MAX;
       for (int d = L.d0; d < L.d1; ++d) {
         const Fam &f = c.fams[size_t(d)];
-        piece.bytes += (f.o_end - f.o_begin) * f.rows * f.run;
-        end = std::max(end, extent(f, true, nb, live));  // source side: the inflow buffer
-        if (piece.bytes >= kPipeBytes || d + 1 == L.d1) {
-          piece.d1 = d + 1;
-          pieces.push_back({end, nullptr, piece});
-          piece.d0 = d + 1;
-          piece.bytes = 0;
-          end = 0;
+        const uint64_t bytes = (f.o_end - f.o_begin) * f.rows * f.run;
+        const uint64_t lo = f.src_off, hi = extent(f, true, nb, live);  // source side: the inflow buffer
+        const uint64_t span = std::max(p.end, hi) - std::min(begin, lo);
+        if (p.L.bytes && (p.L.bytes >= kPipeBytes || span > std::max(2 * (p.L.bytes + bytes), kPipeBytes))) {
+          p.L.d1 = d;
+          pieces.push_back(p);
+          p.L.d0 = d;
+          p.L.bytes = p.end = 0;
+          begin = UINT64_MAX;
         }
+        p.L.bytes += bytes;
+        p.end = std::max(p.end, hi);
+        begin = std::min(begin, lo);
       }
+      p.L.d1 = L.d1;
+      pieces.push_back(p);
     }
     std::stable_sort(pieces.begin(), pieces.end(), [](const Piece &x, const Piece &y) { return x.end < y.end; });
+    // neighbours in both orders go as one launch
+    size_t n = 0;
+    for (const Piece &x : pieces) {
+      Piece *y = n ? &pieces[n - 1] : nullptr;
+      if (y && !x.direct && !y->direct && y->L.d1 == x.L.d0 && y->L.aligned == x.L.aligned && y->L.wide == x.L.wide &&
+          y->L.bytes + x.L.bytes <= kPipeBytes && x.end - y->end <= kPipeBytes) {
+        y->L.d1 = x.L.d1;
+        y->L.bytes += x.L.bytes;
+        y->L.tiles_max += x.L.tiles_max;
+        y->end = x.end;
+      } else {
+        pieces[n++] = x;
+      }
+    }
+    pieces.resize(n);
     for (const Piece &x : pieces) {
       await(x.end);
       if (x.direct) {

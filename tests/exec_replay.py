@@ -24,6 +24,7 @@ import numpy as np  # noqa: E402
 
 from paper_2511_11617_amd import atp, problem  # noqa: E402
 from synth import checkpoint, configs, pagetable  # noqa: E402
+from tests.schedule_sim import H2D, copies  # noqa: E402
 
 
 def dmalloc(n):
@@ -120,6 +121,9 @@ def run(case):
         roles = {s1: "copy", s0: "compute"}
         log = {"log": [(n, int(k), roles.get(int(s), "side")) for n, k, s in
                        (x.split() for x in mock.mock_log().decode().splitlines())]}
+        log["reads"] = [(x.src_off, x.src_off + (x.item_end - x.item_begin - 1) * x.src_stride + (x.rows - 1) *
+                         x.src_pitch + x.run, (x.item_end - x.item_begin) * x.rows * x.run)
+                        for x in copies(p, 0) if x.op == H2D]
     return {"ok": True, **log, "launches": launches, "mock_launches": int(mock.mock_launches()),
             "mock_copies": int(mock.mock_copies()), "streams": int(mock.mock_streams())}
 

@@ -10,7 +10,8 @@
 //     launches need a non-empty grid.  A violation prints MOCKHIP FAULT and
 //     aborts the process.
 //   * Kernels are counted, not run; events time 0.125 ms.
-//   * mock_log() lists the launches ("kernel name, workgroups, stream") and
+//   * mock_log() lists the launches ("kernel name, workgroups, stream", the
+//     copy kernels' names with the first descriptor and the one past the last) and
 //     copies ("copy, bytes, stream") since mock_log_clear(), one a line.
 #include <hip/hip_runtime_api.h>
 #include <cstdio>
@@ -151,12 +152,15 @@ hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind k, hip
   log_text += "copy " + std::to_string(n) + " " + std::to_string(uintptr_t(st)) + "\n";
   return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **, size_t, hipStream_t s) {
+hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t, hipStream_t s) {
   std::lock_guard<std::mutex> lk(mu);
   if (s && !streams.count(s)) die("launch on an unknown stream", s, 0);
   if (g.x == 0 || b.x == 0) die("empty launch", nullptr, 0);
   ++launches;
-  log_text += names[f] + " " + std::to_string(g.x) + " " + std::to_string(uintptr_t(s)) + "\n";
+  std::string name = names[f];
+  if (name.find("k_copy") != std::string::npos && name.find("linear") == std::string::npos)
+    name += ":" + std::to_string(*static_cast<int *>(args[2])) + ":" + std::to_string(*static_cast<int *>(args[3]));
+  log_text += name + " " + std::to_string(g.x) + " " + std::to_string(uintptr_t(s)) + "\n";
   return hipSuccess;
 }
 hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t sh, hipStream_t s) {

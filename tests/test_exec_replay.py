@@ -139,6 +139,27 @@ def test_outbound_reads_of_a_weights_call_alone_get_their_whole_grid(mockhip):
     assert {g for n, g in side if "k_copy_linkILi2" in n} == {4}, side
 
 
+def test_awaited_reads_in_place_follow_the_buffer(mockhip, tmp_path):
+    """While the inflow buffer is filled from files, the weight pieces of an
+    in-place call go out in the order in which the buffer fills, each reading
+    the buffer in about one place, not in the order their places get free."""
+    r, = _replay(mockhip, [{"w": 5, "inplace": True, "order": "async-load", "steps": 1, "warmup": False, "layers": 24,
+                            "log": True, "shape": {"hidden": 2048, "ffn": 5632, "n_q": 16, "n_kv": 8, "n_seq": 2,
+                                                   "seq_tokens": 64}}], tmp_path)
+    n = len(r["reads"])
+    assert sum(b for _, _, b in r["reads"]) > 200e6
+    spans = [tuple(map(int, k.split(":")[1:])) for k, g, s in r["log"] if s == "side" and "k_copy" in k]
+    # the weights' reads are the last descriptors launched, and no others come after them on that stream
+    d0 = max(d1 for _, d1 in spans) - n
+    pieces = [(a - d0, b - d0) for a, b in spans if a >= d0]
+    assert sorted(x for a, b in pieces for x in range(a, b)) == list(range(n))
+    ends = [max(e for _, e, _ in r["reads"][a:b]) for a, b in pieces]
+    assert ends == sorted(ends)
+    for a, b in pieces:
+        lo, hi = min(s for s, _, _ in r["reads"][a:b]), max(e for _, e, _ in r["reads"][a:b])
+        assert hi - lo <= max(2 * sum(x for _, _, x in r["reads"][a:b]), 64 << 20)
+
+
 def test_many_descriptors_go_to_the_device_by_a_copy_command(mockhip):
     case = {"w": 1, "inplace": True, "order": "weights-first", "steps": 1, "warmup": False, "log": True}
     many, few = _replay(mockhip, [dict(case, shape=late_gates_cfg()), dict(case, shape=late_gates_cfg(
