@@ -1009,6 +1009,10 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
     pa.n_blocks = P.kv.num_blocks;
     pa.expect_live = P.kv.live_blocks;
   }
+  if (kvcall && pa.n_blocks > kPrepWindow) {
+    hipLaunchKernelGGL(k_mark_pool, dim3(1), dim3(kPrepThreads), 0, compute, pa);
+    HIPCHK(hipGetLastError());
+  }
   // k_prepare is the only writer of the error word: it stores it once
   hipLaunchKernelGGL(k_prepare, dim3(1), dim3(kPrepThreads), 0, compute, pa);
   HIPCHK(hipGetLastError());
@@ -1386,6 +1390,7 @@ void exec_warmup(void *compute_, void *copy_, int events) {
   HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy16<kWideUnroll>)));
   HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy_any)));
   HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy_linear)));
+  HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_mark_pool)));
   HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_prepare)));
   HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_spin)));
   HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_nop)));

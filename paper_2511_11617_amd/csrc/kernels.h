@@ -7,6 +7,7 @@
 //                 blocks (wavefront prefix sums over block flags), resolves
 //                 block-id ranges into list positions and scans the tile
 //                 counts of every descriptor (wavefront prefix sums).
+//   k_mark_pool   before it, the block flags of a pool too large for its LDS.
 //   k_copy16      descriptor-driven copy in 16-byte chunks, 2 independent
 //                 loads in flight per thread, non-temporal hints; a tile is
 //                 512 consecutive chunks (8 KiB) of one descriptor.
@@ -105,7 +106,7 @@ constexpr int kPrepGroups = 8;  // groups of 64 ids in flight per wave
 // Table entries [e, e + 1024 K), K loads in flight per thread: marks the ids
 // below n (in LDS or in memory) and keeps the largest id seen.
 template <int K, typename Flags>
-__device__ __forceinline__ void mark_blocks(const PrepArgs &a, int64_t e, int64_t n, Flags flag, int32_t *top) {
+__device__ __forceinline__ void mark_blocks(const PrepArgs &a, int64_t e, uint32_t n, Flags flag, int32_t *top) {
   int32_t v[K];
 #pragma unroll
   for (int k = 0; k < K; ++k) {
@@ -115,15 +116,15 @@ __device__ __forceinline__ void mark_blocks(const PrepArgs &a, int64_t e, int64_
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     *top = v[k] > *top ? v[k] : *top;
-    if (v[k] >= 0 && v[k] < n) flag[v[k]] = 1;
+    if (uint32_t(v[k]) < n) flag[uint32_t(v[k])] = 1;  // n is at most 2^31: no negative id is below it
   }
 }
 
-// The whole table.
+// The whole table: the widest batches first, then one as wide as the rest needs.
 template <typename Flags>
-__device__ __forceinline__ void mark_table(const PrepArgs &a, int64_t n, Flags flag, int32_t *top) {
+__device__ __forceinline__ void mark_table(const PrepArgs &a, uint32_t n, Flags flag, int32_t *top) {
   constexpr int nt = kPrepThreads;
-  int64_t e = 0;  // the widest batches first, then one as wide as the rest needs
+  int64_t e = 0;
   for (; a.n_entries - e >= int64_t(nt) * 16; e += int64_t(nt) * 16) mark_blocks<16>(a, e, n, flag, top);
   const int64_t rest = a.n_entries - e;
   if (rest > nt * 8)
@@ -140,8 +141,26 @@ __device__ __forceinline__ void mark_table(const PrepArgs &a, int64_t n, Flags f
 // live list's room.  The list grows 4 bytes per live id from the front, so
 // that after the ids below w it ends at most at 4 w, below the flags of the
 // ids from w on.
-__device__ __forceinline__ uint8_t *pool_flags(const PrepArgs &a) {
-  return reinterpret_cast<uint8_t *>(a.live) + 3 * flag_room(a.n_blocks);
+__device__ __forceinline__ global_u8 *pool_flags(const PrepArgs &a) {
+  return (global_u8 *)(reinterpret_cast<uint8_t *>(a.live) + 3 * flag_room(a.n_blocks));
+}
+
+// Before k_prepare where the pool is larger than one window: the flags, and
+// the largest id of the table in rank[0].  One workgroup (a barrier lies
+// between clearing and marking), in a kernel of its own so that the small
+// pools' k_prepare stays small.
+__global__ void __launch_bounds__(kPrepThreads) k_mark_pool(PrepArgs a) {
+  __shared__ int32_t s_top;
+  global_u8 *flags = pool_flags(a);
+  if (threadIdx.x == 0) s_top = -1;
+  for (int64_t i = threadIdx.x; i < flag_room(a.n_blocks) / 16; i += kPrepThreads)
+    ((global_u32x4 *)flags)[i] = u32x4{0, 0, 0, 0};
+  __syncthreads();
+  int32_t top = -1;
+  mark_table(a, uint32_t(a.n_blocks < (int64_t(1) << 31) ? a.n_blocks : int64_t(1) << 31), flags, &top);
+  atomicMax(&s_top, top);
+  __syncthreads();
+  if (threadIdx.x == 0) a.rank[0] = s_top;
 }
 
 // One workgroup, bound by the latency of its loads and by what one CU moves.
@@ -157,8 +176,8 @@ __device__ __forceinline__ uint8_t *pool_flags(const PrepArgs &a) {
 // cache lines of flags in memory).  Each wave then turns 64 bytes into a
 // mask with a ballot, one scan over the groups gives their ranks, and a wave
 // writes the ids of a group to consecutive places.  A pool beyond kPrepWindow
-// ids is marked in memory in one pass over the table and taken window by window
-// from there (a pass over the table per window took longer from about the third
+// ids is marked in memory (k_mark_pool) in one pass over the table and taken window
+// by window from there (a pass over the table per window took longer from about the third
 // window on, and more the emptier the table is).
 __global__ void __launch_bounds__(kPrepThreads) k_prepare(PrepArgs a) {
   __shared__ int64_t s64[16];
@@ -190,23 +209,17 @@ __global__ void __launch_bounds__(kPrepThreads) k_prepare(PrepArgs a) {
   if (a.kv) {
     int32_t top = -1;
     const bool one_window = a.n_blocks <= kPrepWindow;
-    global_u8 *flags = (global_u8 *)pool_flags(a);
-    if (!one_window) {
-      for (int64_t i = tid; i < flag_room(a.n_blocks) / 16; i += nt) ((global_u32x4 *)flags)[i] = u32x4{0, 0, 0, 0};
-      __syncthreads();
-      mark_table(a, a.n_blocks, flags, &top);
-      __syncthreads();
-    }
+    if (!one_window) top = a.rank[0];
     for (int64_t w0 = 0; w0 < a.n_blocks; w0 += kPrepWindow) {
       const int n = int(a.n_blocks - w0 < kPrepWindow ? a.n_blocks - w0 : kPrepWindow);
       const int groups = (n + 63) >> 6;
       if (one_window) {
         for (int i = tid; i < groups * 4; i += nt) reinterpret_cast<u32x4 *>(s_flag)[i] = u32x4{0, 0, 0, 0};
         __syncthreads();
-        mark_table(a, n, s_flag, &top);
+        mark_table(a, uint32_t(n), s_flag, &top);
       } else {
         for (int i = tid; i < groups * 4; i += nt)
-          reinterpret_cast<u32x4 *>(s_flag)[i] = ((const global_u32x4 *)(flags + w0))[i];
+          reinterpret_cast<u32x4 *>(s_flag)[i] = ((const global_u32x4 *)(pool_flags(a) + w0))[i];
       }
       __syncthreads();
       for (int g = wave * kPrepGroups; g < groups; g += kPrepGroups * (nt >> 6)) {

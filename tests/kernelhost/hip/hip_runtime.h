@@ -26,6 +26,7 @@ void __threadfence_system();
 uint64_t __ballot(int);
 inline int __popcll(uint64_t v) { return __builtin_popcountll(v); }
 int atomicOr(int *, int);
+int atomicMax(int *, int);
 
 #define __HIP_MEMORY_SCOPE_SYSTEM 0
 #define __hip_atomic_load(p, order, scope) (*(p))

@@ -160,6 +160,14 @@ def test_awaited_reads_in_place_follow_the_buffer(mockhip, tmp_path):
         assert hi - lo <= max(2 * sum(x for _, _, x in r["reads"][a:b]), 64 << 20)
 
 
+@pytest.mark.parametrize("blocks", [65536, 65537, 300000])
+def test_a_large_pool_is_marked_by_one_launch(mockhip, blocks):
+    """One pass over the block table, whatever the number of windows."""
+    r, = _replay(mockhip, [{"w": 1, "inplace": False, "order": "kv-only", "steps": 1, "warmup": False, "layers": 1,
+                            "log": True, "shape": {"block_tokens": 1, "n_seq": 1, "seq_tokens": blocks}}])
+    assert sum("k_mark_pool" in n for n, g, s in r["log"]) == int(blocks > 65536)
+
+
 def test_many_descriptors_go_to_the_device_by_a_copy_command(mockhip):
     case = {"w": 1, "inplace": True, "order": "weights-first", "steps": 1, "warmup": False, "log": True}
     many, few = _replay(mockhip, [dict(case, shape=late_gates_cfg()), dict(case, shape=late_gates_cfg(
