@@ -539,9 +539,11 @@ void launch_copy(const Launch &L, const Desc *dev_desc, const int64_t *dev_prefi
     hipLaunchKernelGGL(kernel, g, dim3(kThreads), 0, s, dev_desc, dev_prefix, L.d0, L.d1, b0, b1, b2, live, more...);
   };
   if (!L.aligned)
-    go(k_copy_any, calm);
-  else if (link && (L.wide || link->two))
-    L.wide ? go(k_copy_link<kWideUnroll>, calm) : go(k_copy_link<kUnroll>, calm);
+    calm ? go(k_copy_any<true>, calm) : go(k_copy_any<false>, calm);
+  else if (link && L.wide)
+    go(k_copy_link<kWideUnroll, false>, calm);
+  else if (link && link->two)
+    calm ? go(k_copy_link<kUnroll, true>, calm) : go(k_copy_link<kUnroll, false>, calm);
   else
     L.wide ? go(k_copy16<kWideUnroll>) : go(k_copy16<kUnroll>);
   HIPCHK(hipGetLastError());
@@ -1009,12 +1011,13 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
     pa.n_blocks = P.kv.num_blocks;
     pa.expect_live = P.kv.live_blocks;
   }
-  if (kvcall && pa.n_blocks > kPrepWindow) {
+  const bool marked = kvcall && pa.n_blocks > kPrepWindow;
+  if (marked) {
     hipLaunchKernelGGL(k_mark_pool, dim3(1), dim3(kPrepThreads), 0, compute, pa);
     HIPCHK(hipGetLastError());
   }
   // k_prepare is the only writer of the error word: it stores it once
-  hipLaunchKernelGGL(k_prepare, dim3(1), dim3(kPrepThreads), 0, compute, pa);
+  hipLaunchKernelGGL(marked ? k_prepare<true> : k_prepare<false>, dim3(1), dim3(kPrepThreads), 0, compute, pa);
   HIPCHK(hipGetLastError());
   is.other(compute);
   // descriptors, prefix sums and live blocks in place: the side stream waits
@@ -1384,14 +1387,17 @@ void exec_warmup(void *compute_, void *copy_, int events) {
   Exec E;  // hands its events back to the device pool when it goes
   HIPCHK(hipGetDevice(&E.device));
   hipFuncAttributes fa;
-  HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy_link<kUnroll>)));
-  HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy_link<kWideUnroll>)));
+  HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy_link<kUnroll, false>)));
+  HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy_link<kUnroll, true>)));
+  HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy_link<kWideUnroll, false>)));
   HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy16<kUnroll>)));
   HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy16<kWideUnroll>)));
-  HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy_any)));
+  HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy_any<false>)));
+  HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy_any<true>)));
   HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy_linear)));
   HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_mark_pool)));
-  HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_prepare)));
+  HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_prepare<false>)));
+  HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_prepare<true>)));
   HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_spin)));
   HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_nop)));
   choose_side(E, compute, copy);

@@ -179,6 +179,8 @@ __global__ void __launch_bounds__(kPrepThreads) k_mark_pool(PrepArgs a) {
 // ids is marked in memory (k_mark_pool) in one pass over the table and taken window
 // by window from there (a pass over the table per window took longer from about the third
 // window on, and more the emptier the table is).
+// MARKED: k_mark_pool has set the flags of the pool.
+template <bool MARKED>
 __global__ void __launch_bounds__(kPrepThreads) k_prepare(PrepArgs a) {
   __shared__ int64_t s64[16];
   __shared__ int32_t s32[16];
@@ -208,12 +210,11 @@ __global__ void __launch_bounds__(kPrepThreads) k_prepare(PrepArgs a) {
   int64_t n_live = 0;
   if (a.kv) {
     int32_t top = -1;
-    const bool one_window = a.n_blocks <= kPrepWindow;
-    if (!one_window) top = a.rank[0];
+    if (MARKED) top = a.rank[0];
     for (int64_t w0 = 0; w0 < a.n_blocks; w0 += kPrepWindow) {
       const int n = int(a.n_blocks - w0 < kPrepWindow ? a.n_blocks - w0 : kPrepWindow);
       const int groups = (n + 63) >> 6;
-      if (one_window) {
+      if (!MARKED) {  // one window
         for (int i = tid; i < groups * 4; i += nt) reinterpret_cast<u32x4 *>(s_flag)[i] = u32x4{0, 0, 0, 0};
         __syncthreads();
         mark_table(a, uint32_t(n), s_flag, &top);
@@ -512,9 +513,11 @@ __device__ __forceinline__ void store16_any(char *p, u32x4 v) {
   __builtin_nontemporal_store(v, (global_u32x4_any *)(p));
 }
 
-// Whether a launch is to go at half its rate: a word in pinned host memory
-// (null: no), looked at every kCalmTiles tiles.  Each wave decides for itself.
+// Whether a launch is to go at half its rate: a word in pinned host memory,
+// looked at every kCalmTiles tiles.  Each wave decides for itself.  (Only the
+// CALM kernels look: the others' loops stay as they are without it.)
 constexpr uint32_t kCalmTiles = 32;
+template <bool CALM>
 struct Calm {
   const int32_t *word;
   uint32_t n = 0;
@@ -522,7 +525,8 @@ struct Calm {
 
   __device__ __forceinline__ explicit Calm(const int32_t *w) : word(w) {}
   __device__ __forceinline__ bool poll() {
-    if (word && n++ % kCalmTiles == 0) {
+    if (!CALM) return false;
+    if (n++ % kCalmTiles == 0) {
       now = seen;  // the read before this one: it has long arrived
       seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
       if (n == 1) now = seen;
@@ -540,12 +544,13 @@ __device__ __forceinline__ void copy_short_lines(const Desc &x, uint64_t c0, uin
   }
 }
 
+template <bool CALM>
 __global__ void __launch_bounds__(kThreads) k_copy_any(const Desc *__restrict__ descs,
                                                        const int64_t *__restrict__ prefix, int d0, int d1, char *b0,
                                                        char *b1, char *b2, const int32_t *__restrict__ live,
                                                        const int32_t *calm) {
   constexpr int U = kUnroll;
-  Calm slow(calm);
+  Calm<CALM> slow(calm);
   const int64_t T0 = prefix[d0], T1 = prefix[d1];
   for (int64_t t = T0 + tile_of_block(); t < T1; t += gridDim.x) {
     const int d = find_desc(prefix, d0, d1, t);
@@ -602,7 +607,7 @@ struct LinkTile {
   }
 };
 
-template <int U>
+template <int U, bool CALM>
 __global__ void __launch_bounds__(kThreads) k_copy_link(const Desc *__restrict__ descs,
                                                         const int64_t *__restrict__ prefix, int d0, int d1, char *b0,
                                                         char *b1, char *b2, const int32_t *__restrict__ live,
@@ -611,7 +616,7 @@ __global__ void __launch_bounds__(kThreads) k_copy_link(const Desc *__restrict__
   int64_t t = prefix[d0] + tile_of_block();
   if (t >= T1) return;
   int d = find_desc(prefix, d0, d1, t);
-  Calm one(calm);
+  Calm<CALM> one(calm);
   LinkTile<U> x, y;
   x.load(descs[d], t - prefix[d], b0, b1, b2, live);
   for (;;) {
