@@ -192,6 +192,10 @@ void atp_plan_free(atp_plan_t *plan);
  * writes the outbound bytes: both host buffers must come from hipHostMalloc
  * (device-accessible at the same address) and be 256-byte aligned, else
  * ATP_EINVAL / ATP_EALIGN.
+ * With ATP_INPLACE the call's order on the link takes the KV call that the
+ * plan describes to follow: where the KV inflow outlasts the outbound reads,
+ * the weight inflow comes after those.  For weights alone, a plan without KV
+ * reads both at once (17.9 ms instead of 23.9 for 721 MB in and 587 MB out).
  * Launch errors return ATP_EHIP once the work the call had already queued
  * has drained (the plan is then not pending); kernel-side errors surface in
  * atp_sync. */

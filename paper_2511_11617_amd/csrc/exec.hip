@@ -850,7 +850,7 @@ void exec_call(Plan &P, bool kvcall, void *arena, uint64_t arena_bytes, void *ne
   // the copy stream: the ring's copies ran at 57 GB/s in some processes and
   // at 30 in others, for all of a process's passes after the first, so that
   // the 4-layer TP 8->7 reshard in place took 52.1 ms a step or 81.9; read
-  // by the kernel it takes 51.4 (80 layers: 1017 -> 1008).
+  // by the kernel it takes 50.3-51.0 (80 layers: 1018-1038, now 1014-1022).
   const bool ring_pinned = !c.chunks.empty() && kernel_readable(inflow_host, inflow_bytes) &&
                            one_allocation(inflow_host, inflow_bytes);
   // The first ones may land in their slots all the same, read by the copy
