@@ -30,13 +30,16 @@ def _ragged(head_dim):
 
 @pytest.mark.parametrize("memory", ["pinned", "pageable", "misaligned"])
 @pytest.mark.parametrize("name", ["ring-of-16-chunks", "odd-pieces", "one-odd-head", "late-gates",
-                                  "late-gates-last-tile", "late-gates-four-slots", "wide-lines"])
+                                  "late-gates-last-tile", "late-gates-four-slots", "outbound-beside", "wide-lines"])
 def test_in_place_kv_inflow(name, memory):
     cfg, cap = {"ring-of-16-chunks": (squeezed_ring_cfg(), SQUEEZED_RING_CAP),
                 "odd-pieces": (_ragged(7), 1 << 30),
                 "one-odd-head": (dict(_ragged(20), layers=1), 1 << 30),
                 "late-gates": (late_gates_cfg(), 1 << 30),
                 "late-gates-last-tile": (late_gates_cfg(head_dim=12), 1 << 30),  # not whole tiles of 8 KiB
+                "outbound-beside": (late_gates_cfg(n_q=16, n_kv=8, head_dim=80, layers=4, n_seq=4, seq_tokens=2048,
+                                                   fragmented=False, pool_factor=1.0, block_tokens=16,
+                                                   new_kv_widths=[4, 4], kv_rule="widths"), 1 << 30),
                 "late-gates-four-slots": (late_gates_cfg(layers=2), 24 << 20),
                 "wide-lines": (configs.scaled(5, layers=2, n_seq=2, seq_tokens=1024, kv_kind=KIND_RAW16),
                                1 << 30)}[name]
