@@ -89,6 +89,7 @@ struct DevicePool {
   std::vector<hipStream_t> streams;  // side streams (choose_side); never destroyed, so that no new
                                      // stream reuses a handle the probe cache knows
   std::vector<std::pair<void *, size_t>> pinned;
+  bool kernels_loaded = false;  // by atp_warmup
 };
 std::mutex g_pool_mu;
 std::map<int, DevicePool> g_pools;
@@ -1386,20 +1387,32 @@ void exec_warmup(void *compute_, void *copy_, int events) {
   hipStream_t compute = static_cast<hipStream_t>(compute_), copy = static_cast<hipStream_t>(copy_);
   Exec E;  // hands its events back to the device pool when it goes
   HIPCHK(hipGetDevice(&E.device));
-  hipFuncAttributes fa;
-  HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy_link<kUnroll, false>)));
-  HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy_link<kUnroll, true>)));
-  HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy_link<kWideUnroll, false>)));
-  HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy16<kUnroll>)));
-  HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy16<kWideUnroll>)));
-  HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy_any<false>)));
-  HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy_any<true>)));
-  HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_copy_linear)));
-  HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_mark_pool)));
-  HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_prepare<false>)));
-  HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_prepare<true>)));
-  HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_spin)));
-  HIPCHK(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(&k_nop)));
+  // each kernel's code, once per device: a later call finds it loaded
+  bool load = false;
+  {
+    std::lock_guard<std::mutex> g(g_pool_mu);
+    load = !g_pools[E.device].kernels_loaded;
+  }
+  if (load) {
+    hipFuncAttributes fa;
+    for (const void *f : {
+             reinterpret_cast<const void *>(&k_copy_link<kUnroll, false>),
+             reinterpret_cast<const void *>(&k_copy_link<kUnroll, true>),
+             reinterpret_cast<const void *>(&k_copy_link<kWideUnroll, false>),
+             reinterpret_cast<const void *>(&k_copy16<kUnroll>),
+             reinterpret_cast<const void *>(&k_copy16<kWideUnroll>),
+             reinterpret_cast<const void *>(&k_copy_any<false>),
+             reinterpret_cast<const void *>(&k_copy_any<true>),
+             reinterpret_cast<const void *>(&k_copy_linear),
+             reinterpret_cast<const void *>(&k_mark_pool),
+             reinterpret_cast<const void *>(&k_prepare<false>),
+             reinterpret_cast<const void *>(&k_prepare<true>),
+             reinterpret_cast<const void *>(&k_spin),
+             reinterpret_cast<const void *>(&k_nop)})
+      HIPCHK(hipFuncGetAttributes(&fa, f));
+    std::lock_guard<std::mutex> g(g_pool_mu);
+    g_pools[E.device].kernels_loaded = true;
+  }
   choose_side(E, compute, copy);
   choose_reads(E);
   (void)scratch_of(E.device);  // the no-allocation entry point's scratch array, on this device
